@@ -102,8 +102,8 @@ typedef struct pi_info {
   double ms;                 /* wall time of the call, host clock, milliseconds */
   int32_t status;            /* pi_status of this instance                      */
   int32_t components;        /* connected groups of data cells                  */
-  int32_t worklist_rebuilds; /* batched calls: times the work list was shrunk
-                                to the unfinished instances (0 for pi_solve)   */
+  int32_t worklist_rebuilds; /* batched calls: times finished instances left the
+                                work list while others ran (0 for pi_solve)    */
   int32_t reserved;
 } pi_info;
 
@@ -153,6 +153,13 @@ pi_status pi_set_inner_iters(pi_plan_t plan, int32_t iters);
  * face-crossing scheme: twice the waves of 4 at the same segment length),
  * 0 picks 4 when allowed, else 1.  The autotuner sweeps both knobs.
  * Returns PI_ERR_INVALID_ARG for other values.
+ * Solves whose vectors fit the registers of the device run on the chip, in
+ * one kernel without a tile (CG in the face-crossing scheme: FP32 up to 4 M
+ * cells in 2-D and 2 M in 3-D; FP64 up to half of that, without a mask or
+ * with PI_FIXED_POINT_CG), while mseg and lane_cells are both 0, the
+ * default.  A tile asked for here is used: the solve then streams its vectors
+ * through memory.  Either way the arithmetic per cell is the same; the FP64
+ * sums are added in another order.
  * Rebuilds the plan's block table (synchronous): PI_ERR_OOM if that fails,
  * and then pi_solve, pi_source, pi_apply and pi_time_kernel on the plan
  * return PI_ERR_OOM until a later pi_set_tile succeeds.
@@ -193,7 +200,9 @@ int32_t pi_get_lane_cells(pi_plan_t plan);
  * itself: the call enqueues enough outer-step replays to reach max_iter
  * (<= 2^22), every kernel of which returns at once after the stop, then the
  * gauge and a copy of the final state.  A loose max_iter therefore costs
- * about 0.3 ms of empty launches per 8 unneeded outer steps at 256^3.  After
+ * about 0.3 ms of empty launches per 8 unneeded outer steps at 256^3 (on the
+ * chip, an empty launch of about 20 us per 4096 / (inner iterations + 1)
+ * outer steps).  After
  * the stream has completed, P holds the result and pi_last_info gives its
  * pi_info (ms = 0) and status.  Without PI_ASYNC the call returns once the
  * solve is done: it polls the convergence flag between replays and never
@@ -217,7 +226,11 @@ pi_status pi_last_info(pi_plan_t plan, pi_info *info);
  * replayed.  A finished instance's tiles return at once; when finished
  * instances hold a quarter of the listed tiles, the host (between replays)
  * rebuilds the work list without them and captures the graph again
- * (pi_info.worklist_rebuilds counts this).
+ * (pi_info.worklist_rebuilds counts this).  Instances that pi_solve would
+ * solve on the chip (see pi_set_tile) are solved there first, as many side by
+ * side as the device holds; a finished one gives up its place at once, and
+ * pi_info.worklist_rebuilds counts these too.  An instance returns what its
+ * own pi_solve returns, bit for bit, when both run on the chip.
  *   count         number of instances (>= 1); plans[i] must be distinct and
  *                 share the precision flag.
  *   gx, gy, gz, P host arrays of `count` device pointers, as for pi_solve

@@ -39,6 +39,15 @@ constexpr int kShapeCC = 12;
 constexpr int kInlineMaxBlocks = 1024;
 constexpr int32_t kNoStop = 1 << 30;
 
+// On-chip solve (pi_resident.hip): threads of a workgroup, workgroups of a
+// launch at most (one per CU), ring cells per lane in 3-D, LDS bytes of a tile at most.
+constexpr int kResBlock = 1024;
+constexpr int kResMaxWg = 256;
+constexpr int kResRing3 = 3;
+constexpr int kResLds = 150 * 1024;
+constexpr int kResGroup = 16;  // workgroups whose sums are added first where there are more than 64
+constexpr int kResGroups = kResMaxWg / kResGroup;
+
 // CG passes that evaluate q again (k_cg_rq): the layers next to the y faces
 // (rows 0..2 and ny-3..ny-1, every plane, in chunks of kRqChunk planes) and
 // next to the march faces (planes 0..2 and nm-3..nm-1 of the other rows) are
@@ -209,6 +218,15 @@ struct Inst {
   void *q1;         // CG: second M p buffer (ping-pong with q)
   void *d;          // correction accumulated by the inner solve
   void *bs[4];      // BiCGStab: rhat, v, s, t
+  // on-chip solve (pi_resident.hip); res_nwg == 0: the grid streams
+  int32_t res_nwg;        // workgroups
+  int32_t res_n;          // cells per lane the code is compiled for (>= res_r)
+  int32_t res_tx, res_ty; // cells of a workgroup's box along x and (3-D) y
+  int32_t res_g, res_r;   // ... and along the march axis: res_g groups of lanes, res_r cells per lane
+  int32_t res_bx, res_by; // boxes along x, y
+  int64_t res_words;      // exchange words of one tag parity: [res_nwg + kResGroups][8] of partial sums,
+                          // then [res_nwg][ring cells] of face cells (two words each in FP64)
+  uint64_t *res_x;        // both parities
   // per-solve user buffers
   const void *g[3];
   void *Pout;
@@ -241,6 +259,7 @@ struct State {
                     // none); passes 0 .. min(stop_at, inner_iters) - 1 ran
   int32_t dvalid;   // BiCGStab: the correction buffer holds this outer step's
                     // sum (an update has run since the outer step began)
+  int64_t tag;      // on-chip solve: synchronisations so far
 };
 
 }  // namespace pi

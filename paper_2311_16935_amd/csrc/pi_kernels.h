@@ -43,6 +43,14 @@ hipError_t launch(KernelId k, bool fp64, int shape, const LaunchArgs &la);
 // as strips.  opl: the fixed point's operator.
 hipError_t launch_cg_rq(bool opl, const LaunchArgs &la);
 
+// The on-chip solve of grids with res_nwg > 0, in outer steps of about
+// `syncs` synchronisations: tab names (instance, workgroup); coop where some
+// grid has several workgroups, and then nwg at most the device's CUs (and
+// kResMaxWg).  lds: the largest res_lds of the instances.
+hipError_t resident_setup();   // before the first launch on the current device
+hipError_t launch_resident(bool fp64, const BlockEnt *tab, const Inst *insts, State *sts, int nwg, bool coop,
+                           size_t lds, int syncs, hipStream_t s);
+
 // Kernels that leave per-block partial sums, and the per-instance finalize
 // (grid = count instances) that turns them into the instances' scalars.
 bool reduces(KernelId k);

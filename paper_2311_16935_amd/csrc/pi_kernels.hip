@@ -22,6 +22,7 @@
 #include <string.h>
 
 #include "pi_common.h"
+#include "pi_device.h"
 #include "pi_kernels.h"
 
 namespace pi {
@@ -188,10 +189,6 @@ __device__ inline Walk make_walk(const Inst &in, int lb) {
   return k;
 }
 
-__device__ inline int dstate(uint32_t code, int d, int bits) {
-  return (int)((code >> (bits * d)) & ((1u << bits) - 1u));
-}
-
 // Counter code of a cell of a grid without missing data, from its
 // coordinates: the same word the plan stores (face neighbour J = C + s e_a
 // inside the grid; laterals of J with data along each remaining axis; far
@@ -215,19 +212,6 @@ __device__ inline uint32_t code_at(int x, int y, int z, int nx, int ny, int nz) 
     out |= state << (bits * d);
   }
   return out;
-}
-
-// Code word of a cell whose face neighbours, their laterals and their far
-// cells all hold data: every direction in its last state.
-template <int ND>
-__host__ __device__ constexpr uint32_t interior_code() {
-  uint32_t c = kValidBit;
-  for (int d = 0; d < 2 * ND; ++d) c |= (ND == 3 ? 18u : 6u) << ((ND == 3 ? 5 : 3) * d);
-  return c;
-}
-template <int ND>
-__host__ __device__ constexpr int interior_state() {
-  return ND == 3 ? 18 : 6;
 }
 
 // What the stencil body sees at one cell: its operand value, the y
@@ -559,30 +543,6 @@ __device__ inline void cg_partials(const Inst &in, const double *part, int j, do
   for (int k = 0; k < 4; ++k) s[k] = tot[k];
 }
 
-// From the sums of CG iteration j: alpha_j = r.r / p.q and, with
-// |r_j - alpha_j q_j|^2 = r.r - 2 alpha_j r.q + alpha_j^2 q.q, beta_{j+1}.
-// The fixed-point variant's inner solve stops once that residual is well
-// below the tolerance (the FP64 outer step then confirms it), or once it is
-// as small as the vector precision can resolve: beyond that only the
-// residual's rounding-level constant part is left, which the singular
-// operator cannot reduce (p.q -> 0 and alpha would blow up); the next outer
-// step restarts from the FP64 residual.
-struct CgScalars {
-  double al, be;
-  bool stop;
-};
-__device__ inline CgScalars cg_scalars(const Inst &in, const State *st, const double (&s)[4]) {
-  const double pq = s[0], rq = s[1], qq = s[2], rr = s[3];
-  const double al = pq != 0.0 ? rr / pq : 0.0;
-  double rn = rr - 2.0 * al * rq + al * al * qq;
-  if (!(rn > 0.0)) rn = 0.0;
-  CgScalars c;
-  c.al = al;
-  c.be = rr != 0.0 ? rn / rr : 0.0;
-  c.stop = in.inner_op != 0 && (rn <= 0.25 * in.tol * in.tol * st->normS2 || rn <= in.inner_floor * st->rr0);
-  return c;
-}
-
 template <typename T>
 __device__ inline void load_lut(const double (*src)[kStates], T (*dst)[kStates]) {
   for (int i = threadIdx.x; i < 6 * kStates; i += kBlock) dst[i / kStates][i % kStates] = (T)src[i / kStates][i % kStates];
@@ -620,13 +580,15 @@ __global__ __launch_bounds__(kBlock) void k_init(const BlockEnt *tab, const Inst
   for (int64_t c = beg + threadIdx.x; c < end; c += kBlock) {
     // no correction before the first outer step, and finite search
     // directions and products for the first inner iteration (which scales
-    // them by 0)
-    d[c] = T(0);
-    p0[c] = T(0);
-    p1[c] = T(0);
-    q0[c] = T(0);
-    if (q1) q1[c] = T(0);
-    if (v) v[c] = T(0);
+    // them by 0); the on-chip solve keeps these in registers
+    if (in.res_nwg == 0) {
+      d[c] = T(0);
+      p0[c] = T(0);
+      p1[c] = T(0);
+      q0[c] = T(0);
+      if (q1) q1[c] = T(0);
+      if (v) v[c] = T(0);
+    }
     double x = 0.0;
     if (warm && (code[c] & kValidBit)) {
       x = (double)P0[c];
@@ -636,6 +598,12 @@ __global__ __launch_bounds__(kBlock) void k_init(const BlockEnt *tab, const Inst
       }
     }
     P[c] = x;
+  }
+  // exchange words of the on-chip solve: tag 0, which it never publishes
+  if (in.res_nwg > 1) {
+    const int64_t per = (2 * in.res_words + in.nblocks - 1) / in.nblocks;
+    const int64_t wb = min(2 * in.res_words, e.lb * per), we = min(2 * in.res_words, wb + per);
+    for (int64_t w = wb + threadIdx.x; w < we; w += kBlock) in.res_x[w] = 0;
   }
   if (bad) atomicOr(&st->nonfinite, 1);
 }
@@ -1839,40 +1807,10 @@ __global__ __launch_bounds__(kBlock) void k_finalize(const Inst *__restrict__ in
         st->status = 3;  // PI_ERR_NONFINITE
       }
       break;
-    case K_OUTER: {
-      const bool hd = st->have_delta != 0;
-      // CG passes of the inner solve that just ended (BiCGStab counts its own)
-      if (hd && !in.bicg) st->inner_total += min(st->stop_at, in.inner_iters);
-      const double epsR = st->normS2 > 0.0 ? sqrt(s[0] / st->normS2) : 0.0;
-      st->epsR = epsR;
-      if (hd) st->epsP = s[3] > 0.0 ? sqrt(s[2] / s[3]) : 0.0;
+    case K_OUTER:
+      outer_scalars(in, st, s);
       st->Pcur ^= 1;
-      if (!isfinite(epsR)) {
-        st->done = 1;
-        st->status = 5;  // PI_ERR_DIVERGED
-      } else if (epsR <= in.tol) {
-        st->done = 1;
-        st->status = 0;
-      } else if (st->outer >= in.max_iter) {
-        st->done = 1;
-        st->status = 4;  // PI_ERR_NOT_CONVERGED
-      } else {
-        st->outer += 1;
-        st->rr = s[1];
-        st->rr0 = s[1];
-        st->inner = 0;
-        st->stop_at = kNoStop;
-        st->dvalid = 0;
-        st->first = 1;
-        st->beta = 0.0;  // the first search direction is the residual itself
-        st->have_delta = 1;
-        // BiCGStab restarts with the new residual as its shadow vector
-        st->rho = s[1];
-        st->alpha = 1.0;
-        st->omega = 1.0;
-      }
       break;
-    }
     case K_CG_STEP: {
       const CgScalars cs = cg_scalars(in, st, s);
       st->alpha = cs.al;

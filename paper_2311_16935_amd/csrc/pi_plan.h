@@ -52,6 +52,9 @@ struct pi_plan_s {
   int ntab = 0;
   pi::BlockEnt *d_tab_rq = nullptr;  // CG passes of a cg_rq plan: boundary-layer blocks, then d_tab's
   int ntab_rq = 0;
+  int32_t res_nwg = 0;             // workgroups of the on-chip solve (0: does not fit; inst.res_nwg: in use)
+  pi::BlockEnt *d_tab_res = nullptr;  // on-chip solve: (0, workgroup) for each
+  uint64_t *res_x = nullptr;          // ... and its exchange words
   pi::State *h_state = nullptr;    // pinned mirror
   hipGraphExec_t graph = nullptr;  // cached outer-step graph
   int graph_key = -1;

@@ -1,0 +1,86 @@
+// Boxes of the on-chip solve (pi_resident.hip): sizes, and their choice.
+#pragma once
+
+#include <algorithm>
+
+#include "pi_common.h"
+
+namespace pi {
+
+// Ring cells of a box: its faces along the march axis, y (3-D) and x.
+__host__ __device__ inline int res_ring(const Inst &in) {
+  const int tm = in.res_g * in.res_r;
+  return in.ndim == 3 ? 2 * (in.res_tx * in.res_ty + in.res_tx * tm + in.res_ty * tm) : 2 * (in.res_tx + tm);
+}
+
+// LDS bytes of a workgroup: the box and its ring of p followed by q of every
+// lane's cells, or in their place P (FP64) of the box and its ring.
+inline size_t res_lds(const Inst &in, bool fp64) {
+  const size_t sx = in.res_tx + 2, sy = in.ndim == 3 ? in.res_ty + 2 : 1;
+  const size_t tile = sx * sy * ((size_t)in.res_g * in.res_r + 2), t = fp64 ? 8 : 4;
+  return std::max(tile * sizeof(double), (tile + (size_t)kResBlock * in.res_r) * t);
+}
+
+// Microseconds of a pass of the on-chip solve, fitted to boxes of every shape:
+// the cells of a lane (more each where they outgrow the registers), and the
+// exchange -- one hop up to 64 workgroups, two beyond -- longer with the ring
+// words a workgroup reads.
+inline double res_cost(int ndim, int r, int ring, int nwg) {
+  const double cell = (r > 8 ? 0.47 : 0.3) * (ndim == 3 ? 1.3 : 1.0);
+  const double wait = nwg == 1 ? 0.0 : nwg <= 64 ? 2.05 : 3.0 + 0.004 * nwg;
+  return 0.45 + cell * r + wait + (nwg == 1 ? 0.0 : ring * (0.0004 + 0.0006 * nwg / 256.0));
+}
+
+// Boxes of a grid (the res_* sizes of Inst; res_nwg = 0 where it does not
+// fit): the cheapest by res_cost of those that cut every axis into equal
+// parts.  cus: CUs of the device.
+inline void set_resident(Inst &in, bool fp64, int cus) {
+  in.res_nwg = 0;
+  if (in.bicg || in.cc) return;
+  const int max_r = in.ndim == 2 ? (fp64 ? 8 : 16) : (fp64 ? 4 : 8);
+  const int max_wg = std::min(cus, kResMaxWg);
+  if (in.ncell > (int64_t)max_wg * kResBlock * max_r) return;
+  const int ring_max = kResBlock * (in.ndim == 3 ? kResRing3 : 1);
+  double best = 1e300;
+  auto consider = [&](int tx, int ty, int g, int r) {
+    const int64_t bx = (in.nx + tx - 1) / tx, by = (in.ndim == 3 ? (in.ny + ty - 1) / ty : 1);
+    const int64_t tm = (int64_t)g * r, bm = (in.nm + tm - 1) / tm;
+    if (bx * by * bm > max_wg) return;
+    Inst c = in;
+    c.res_tx = tx;
+    c.res_ty = ty;
+    c.res_g = g;
+    c.res_r = r;
+    const int ring = res_ring(c);
+    if (ring > ring_max || res_lds(c, fp64) > (size_t)kResLds) return;
+    const int nwg = (int)(bx * by * bm);
+    const double cost = res_cost(in.ndim, r, ring, nwg);
+    if (cost >= best) return;
+    best = cost;
+    in.res_nwg = nwg;
+    in.res_n = r <= 4 ? 4 : r <= 8 ? 8 : 16;
+    in.res_tx = tx;
+    in.res_ty = ty;
+    in.res_g = g;
+    in.res_r = r;
+    in.res_bx = (int)bx;
+    in.res_by = (int)by;
+  };
+  for (int kx = 1; kx <= in.nx && kx <= max_wg; ++kx) {
+    const int tx = (in.nx + kx - 1) / kx;
+    if (tx > 256 || (tx < 16 && kx > 1)) continue;
+    for (int ky = 1; ky <= (in.ndim == 3 ? in.ny : 1) && kx * ky <= max_wg; ++ky) {
+      const int ty = in.ndim == 3 ? (in.ny + ky - 1) / ky : 1;
+      if (tx * ty > kResBlock) continue;
+      const int gmax = kResBlock / (tx * ty);
+      for (int r = 1; r <= max_r; ++r) {
+        // as few lane groups as cover the axis in the number of boxes that all groups would need
+        const int bm = (in.nm + gmax * r - 1) / (gmax * r);
+        const int g = (in.nm + bm * r - 1) / (bm * r);
+        consider(tx, ty, g, r);
+      }
+    }
+  }
+}
+
+}  // namespace pi

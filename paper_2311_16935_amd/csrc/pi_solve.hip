@@ -21,6 +21,7 @@
 
 #include "pi_kernels.h"
 #include "pi_plan.h"
+#include "pi_resident.h"
 
 using namespace pi;
 
@@ -109,6 +110,12 @@ hipError_t capture(const Launcher &L, hipStream_t cap, int inner, bool bicg, hip
   (void)hipGraphDestroy(g);
   return e;
 }
+
+// Synchronisations (2-10 us each) of one on-chip launch, so that other work
+// on the device gets its turn and, in a batch, waiting grids get the
+// workgroups of finished ones.
+constexpr int kResSyncs = 4096;
+int64_t resident_chunk(int inner) { return std::max(1, kResSyncs / (inner + 1)); }
 
 State fresh_state() {
   State s;
@@ -277,8 +284,13 @@ extern "C" pi_status pi_solve(pi_plan_t p, const void *gx, const void *gy, const
   const Launcher L = single_launcher(p);
   if (L.go(K_INIT, stream, (flags & PI_WARM_START) ? 1 : 0) != hipSuccess || L.go(K_SOURCE, stream) != hipSuccess)
     return PI_ERR_DEVICE;
+  const bool resident = p->inst.res_nwg > 0;
+  auto on_chip = [&] {
+    return launch_resident(p->fp64, p->d_tab_res, p->d_inst, p->d_state, p->inst.res_nwg, p->inst.res_nwg > 1,
+                           res_lds(p->inst, p->fp64), kResSyncs, stream);
+  };
   const int key = p->inner_iters * 2 + (p->bicgstab ? 1 : 0);
-  if (!p->graph || p->graph_key != key) {
+  if (!resident && (!p->graph || p->graph_key != key)) {
     if (p->graph) (void)hipGraphExecDestroy(p->graph);
     p->graph = nullptr;
     if (capture(L, cap_stream(p), p->inner_iters, p->bicgstab, &p->graph) != hipSuccess) return PI_ERR_DEVICE;
@@ -289,10 +301,10 @@ extern "C" pi_status pi_solve(pi_plan_t p, const void *gx, const void *gy, const
     // unfinished instance by `unroll`; after the stop every kernel of a
     // replay returns at once), then the gauge and a copy of the final state
     // into the plan's pinned record, all on `stream`
-    const int unroll = unroll_for(p->inner_iters);
+    const int64_t unroll = resident ? resident_chunk(p->inner_iters) : unroll_for(p->inner_iters);
     const int64_t reps = (max_iter + 1 + unroll - 1) / unroll;
     for (int64_t r = 0; r < reps; ++r)
-      if (hipGraphLaunch(p->graph, stream) != hipSuccess) return PI_ERR_DEVICE;
+      if ((resident ? on_chip() : hipGraphLaunch(p->graph, stream)) != hipSuccess) return PI_ERR_DEVICE;
     if (L.go(K_GAUGE_SUM, stream) != hipSuccess || L.go(K_GAUGE_GROUPS, stream) != hipSuccess ||
         L.go(K_GAUGE_APPLY, stream) != hipSuccess ||
         hipMemcpyAsync(p->h_state, p->d_state, sizeof(State), hipMemcpyDeviceToHost, stream) != hipSuccess)
@@ -301,6 +313,18 @@ extern "C" pi_status pi_solve(pi_plan_t p, const void *gx, const void *gy, const
   }
   // h_state holds three records: [0] final snapshot, [1..2] polling buffers
   int64_t launched = 0;
+  if (resident) {
+    do {
+      if (on_chip() != hipSuccess ||
+          hipMemcpyAsync(p->h_state, p->d_state, sizeof(State), hipMemcpyDeviceToHost, stream) != hipSuccess ||
+          hipStreamSynchronize(stream) != hipSuccess)
+        return PI_ERR_DEVICE;
+    } while (!p->h_state->done);
+    const pi_status rc = finish(L, stream, p->d_state, p->h_state, 1);
+    if (rc != PI_OK) return rc;
+    fill_info(info, *p->h_state, p, ms_since(t0));
+    return (pi_status)p->h_state->status;
+  }
   pi_status rc =
       iterate(p->graph, stream, p->d_state, p->h_state + 1, 1, max_iter, unroll_for(p->inner_iters), &launched);
   if (rc != PI_OK) return rc;
@@ -325,6 +349,7 @@ struct BatchSetup {
   bool bicg = false;
   int inner = 1;
   int parts = 0;
+  int64_t on_chip = 0;  // instances solved on the chip
   bool cg_finalize = false;
   std::vector<Inst> host;
   std::vector<int64_t> idx[kShapes];  // batch index of the instances of each launch shape
@@ -359,6 +384,14 @@ struct WorkList {
 
   explicit WorkList(const BatchSetup &b) : live(b.host.size(), 1) {
     for (const auto &h : b.host) listed += h.nblocks;
+  }
+  // without the grids that were solved on the chip
+  void drop_on_chip(const BatchSetup &b) {
+    listed = 0;
+    for (size_t i = 0; i < b.host.size(); ++i) {
+      live[i] = b.host[i].res_nwg == 0;
+      if (live[i]) listed += b.host[i].nblocks;
+    }
   }
   // from a snapshot of the states: shrink now?
   bool shrink(const BatchSetup &b, const State *snap) {
@@ -402,7 +435,8 @@ pi_status batch_setup(int64_t count, const pi_plan_t *plans, const void *const *
     b.host[i] = p->inst;
     if (!set_user(b.host[i], p, gx[i], gy[i], gz ? gz[i] : nullptr, P[i], tol[i], max_iter, flags))
       return PI_ERR_INVALID_ARG;
-    b.inner = std::max(b.inner, p->inner_iters);
+    if (p->inst.res_nwg > 0) ++b.on_chip;
+    else b.inner = std::max(b.inner, p->inner_iters);
   }
   std::vector<Inst *> by[kShapes];
   for (int64_t i = 0; i < count; ++i) {
@@ -430,6 +464,75 @@ pi_status batch_setup(int64_t count, const pi_plan_t *plans, const void *const *
     if (!b.bicg && !h.cg_inline) b.cg_finalize = true;
   }
   return PI_OK;
+}
+
+// Grids that are solved on the chip, several at a time as far as their
+// workgroups fit the device together: the longest sides first (they take the
+// most outer steps), and after each launch waiting grids take the places of
+// finished ones.  `tab` (device) holds kResMaxWg entries, `hst` (host) count
+// states; the launcher's instance records and states are set up.
+struct OnChip {
+  std::vector<int64_t> todo;
+  int left_early = 0;  // times a grid finished while another was running
+
+  explicit OnChip(const BatchSetup &b) {
+    for (size_t i = 0; i < b.host.size(); ++i)
+      if (b.host[i].res_nwg > 0) todo.push_back((int64_t)i);
+    auto side = [&](int64_t i) { return std::max({b.host[i].nx, b.host[i].ny, b.host[i].nz}); };
+    std::stable_sort(todo.begin(), todo.end(), [&](int64_t x, int64_t y) { return side(x) > side(y); });
+  }
+
+  pi_status run(const BatchSetup &b, const Launcher &L, BlockEnt *tab, int max_wg, State *hst, hipStream_t stream) {
+    std::vector<int64_t> on;
+    std::vector<BlockEnt> t;
+    std::vector<int64_t> ends;
+    while (!todo.empty() || !on.empty()) {
+      int used = 0;
+      for (int64_t i : on) used += b.host[i].res_nwg;
+      for (auto it = todo.begin(); it != todo.end();) {
+        if (used + b.host[*it].res_nwg > max_wg) {
+          ++it;
+          continue;
+        }
+        used += b.host[*it].res_nwg;
+        on.push_back(*it);
+        it = todo.erase(it);
+      }
+      t.clear();
+      size_t lds = 0;
+      bool coop = false;
+      for (int64_t i : on) {
+        const Inst &h = b.host[i];
+        for (int w = 0; w < h.res_nwg; ++w) t.push_back(BlockEnt{(int32_t)i, w});
+        lds = std::max(lds, res_lds(h, b.fp64));
+        coop = coop || h.res_nwg > 1;
+      }
+      if (hipMemcpyAsync(tab, t.data(), t.size() * sizeof(BlockEnt), hipMemcpyHostToDevice, stream) != hipSuccess ||
+          launch_resident(b.fp64, tab, L.insts, L.sts, (int)t.size(), coop, lds, kResSyncs, stream) != hipSuccess ||
+          hipMemcpyAsync(hst, L.sts, b.host.size() * sizeof(State), hipMemcpyDeviceToHost, stream) != hipSuccess ||
+          hipStreamSynchronize(stream) != hipSuccess)
+        return PI_ERR_DEVICE;
+      std::vector<int64_t> still;
+      for (int64_t i : on) {
+        if (hst[i].done) ends.push_back(hst[i].tag);
+        else still.push_back(i);
+      }
+      on.swap(still);
+    }
+    std::sort(ends.begin(), ends.end());
+    left_early = (int)(std::unique(ends.begin(), ends.end()) - ends.begin());
+    if (left_early > 0 && ends.size() > 0 && (size_t)b.on_chip == b.host.size()) --left_early;
+    return PI_OK;
+  }
+};
+
+// CUs of the current device, at most kResMaxWg: workgroups of a launch of the on-chip solve.
+int resident_workgroups() {
+  int dev = 0, cus = 0;
+  if (hipGetDevice(&dev) != hipSuccess ||
+      hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess)
+    return 0;
+  return std::min(cus, kResMaxWg);
 }
 
 pi_status batch_report(int64_t count, const pi_plan_t *plans, const State *hst, pi_info *infos,
@@ -462,12 +565,15 @@ extern "C" pi_status pi_solve_batched(int64_t count, const pi_plan_t *plans, con
   hipStream_t cap = nullptr;
   hipGraphExec_t exec = nullptr;
   State *hst = nullptr;
+  BlockEnt *tab_res = nullptr;
+  OnChip chip(b);
   rc = PI_ERR_DEVICE;
   std::vector<State> init(count, fresh_state());
   if (hipMalloc((void **)&L.insts, count * sizeof(Inst)) != hipSuccess ||
       hipMalloc((void **)&L.sts, count * sizeof(State)) != hipSuccess ||
       hipMalloc((void **)&L.part, (size_t)std::max(b.parts, 1) * 3 * 4 * sizeof(double)) != hipSuccess ||
-      hipHostMalloc((void **)&hst, 2 * count * sizeof(State), hipHostMallocDefault) != hipSuccess) {
+      hipHostMalloc((void **)&hst, 2 * count * sizeof(State), hipHostMallocDefault) != hipSuccess ||
+      (b.on_chip > 0 && hipMalloc((void **)&tab_res, kResMaxWg * sizeof(BlockEnt)) != hipSuccess)) {
     rc = PI_ERR_OOM;
     goto done;
   }
@@ -487,12 +593,20 @@ extern "C" pi_status pi_solve_batched(int64_t count, const pi_plan_t *plans, con
     goto done;
   if (L.go(K_INIT, stream, (flags & PI_WARM_START) ? 1 : 0) != hipSuccess || L.go(K_SOURCE, stream) != hipSuccess)
     goto done;
-  if (hipStreamCreateWithFlags(&cap, hipStreamNonBlocking) != hipSuccess) goto done;
+  if (b.on_chip > 0 &&
+      (rc = chip.run(b, L, tab_res, resident_workgroups(), hst, stream)) != PI_OK)
+    goto done;
+  rc = PI_ERR_DEVICE;
+  if (b.on_chip < count && hipStreamCreateWithFlags(&cap, hipStreamNonBlocking) != hipSuccess) goto done;
   {
     WorkList wl(b);
     int64_t launched = 0;
     auto shrink = [&](const State *snap) { return wl.shrink(b, snap); };
-    for (;;) {
+    if (b.on_chip > 0) {
+      wl.drop_on_chip(b);
+      if (upload_live_tables(b, wl, L, stream) != hipSuccess) goto done;
+    }
+    while (b.on_chip < count) {
       if (capture(L, cap, b.inner, b.bicg, &exec) != hipSuccess) {
         rc = PI_ERR_DEVICE;
         goto done;
@@ -527,7 +641,7 @@ extern "C" pi_status pi_solve_batched(int64_t count, const pi_plan_t *plans, con
     }
     rc = finish(L, stream, L.sts, hst, count);
     if (rc != PI_OK) goto done;
-    rc = batch_report(count, plans, hst, infos, t0, wl.rebuilds);
+    rc = batch_report(count, plans, hst, infos, t0, wl.rebuilds + chip.left_early);
   }
 done:
   if (exec) (void)hipGraphExecDestroy(exec);
@@ -536,6 +650,7 @@ done:
   if (L.insts) (void)hipFree(L.insts);
   if (L.sts) (void)hipFree(L.sts);
   if (L.part) (void)hipFree(L.part);
+  if (tab_res) (void)hipFree(tab_res);
   for (int g = 0; g < kShapes; ++g)
     if (L.grp[g].tab) (void)hipFree(L.grp[g].tab);
   if (hst) (void)hipHostFree(hst);
@@ -557,7 +672,8 @@ constexpr size_t align256(size_t v) { return (v + 255) / 256 * 256; }
 constexpr size_t kNaOffSts = align256(kNaInsts * sizeof(Inst));
 constexpr size_t kNaOffPart = kNaOffSts + align256(kNaInsts * sizeof(State));
 constexpr size_t kNaOffTab = kNaOffPart + align256(kNaParts * 3 * 4 * sizeof(double));
-constexpr size_t kNaBytes = kNaOffTab + align256(kNaTab * sizeof(BlockEnt));
+constexpr size_t kNaOffRes = kNaOffTab + align256(kNaTab * sizeof(BlockEnt));
+constexpr size_t kNaBytes = kNaOffRes + align256(kResMaxWg * sizeof(BlockEnt));
 
 }  // namespace
 
@@ -596,13 +712,22 @@ hipError_t noalloc_scratch(unsigned char **out) {
 // memory and checked every `unroll` outer steps, and the work list shrinks
 // as in pi_solve_batched (the tables are rewritten in place).
 pi_status noalloc_iterate(BatchSetup &b, Launcher &L, hipStream_t stream, int64_t count, int64_t max_iter,
-                          int *rebuilds) {
+                          BlockEnt *tab_res, int *rebuilds) {
+  OnChip chip(b);
+  if (b.on_chip > 0) {
+    const pi_status e = chip.run(b, L, tab_res, resident_workgroups(), g_na_host, stream);
+    if (e != PI_OK) return e;
+  }
   const int unroll = unroll_for(b.inner);
   const int64_t bound = max_iter / unroll + 4;
   const size_t bytes = (size_t)count * sizeof(State);
   WorkList wl(b);
-  pi_status rc = PI_ERR_DEVICE;
-  for (int64_t r = 0; r < bound; ++r) {
+  if (b.on_chip > 0) {
+    wl.drop_on_chip(b);
+    if (upload_live_tables(b, wl, L, stream) != hipSuccess) return PI_ERR_DEVICE;
+  }
+  pi_status rc = b.on_chip < count ? PI_ERR_DEVICE : PI_OK;
+  for (int64_t r = 0; r < bound && b.on_chip < count; ++r) {
     if (L.outer_steps(stream, unroll, b.inner, b.bicg) != hipSuccess) return PI_ERR_DEVICE;
     if (hipMemcpyAsync(g_na_host, L.sts, bytes, hipMemcpyDeviceToHost, stream) != hipSuccess ||
         hipStreamSynchronize(stream) != hipSuccess)
@@ -615,7 +740,7 @@ pi_status noalloc_iterate(BatchSetup &b, Launcher &L, hipStream_t stream, int64_
     }
     if (wl.shrink(b, g_na_host) && upload_live_tables(b, wl, L, stream) != hipSuccess) return PI_ERR_DEVICE;
   }
-  *rebuilds = wl.rebuilds;
+  *rebuilds = wl.rebuilds + chip.left_early;
   if (rc != PI_OK) return rc;
   // the gauge runs over every instance
   std::vector<char> all(count, 1);
@@ -676,7 +801,7 @@ extern "C" pi_status pi_solve_batched_noalloc(int64_t count, const pi_plan_t *pl
   if (L.go(K_INIT, stream, (flags & PI_WARM_START) ? 1 : 0) != hipSuccess || L.go(K_SOURCE, stream) != hipSuccess)
     return PI_ERR_DEVICE;
   int rebuilds = 0;
-  rc = noalloc_iterate(b, L, stream, count, max_iter, &rebuilds);
+  rc = noalloc_iterate(b, L, stream, count, max_iter, (BlockEnt *)(base + kNaOffRes), &rebuilds);
   if (rc == PI_OK) rc = finish(L, stream, L.sts, g_na_host, count);
   if (rc == PI_OK) rc = batch_report(count, plans, g_na_host, infos, t0, rebuilds);
   (void)hipStreamSynchronize(stream);
@@ -841,6 +966,11 @@ extern "C" pi_status pi_autotune(pi_plan_t p, int32_t reps, int32_t *mseg_out, v
     if (it != g_tune.end()) best = it->second;
   }
   pi_status rc;
+  if (p->res_nwg > 0) {  // solved on the chip: the solve has no tile to time
+    rc = pi_set_tile(p, 0, 0);
+    if (rc == PI_OK && mseg_out) *mseg_out = p->inst.mseg;
+    return rc;
+  }
   if (best[0] < 0) {
     std::vector<std::array<int32_t, 2>> cand;
     p->inst.nt_outer = 0;
