@@ -19,52 +19,13 @@
 #include <algorithm>
 
 #include "../../include/pi_unet.h"
+#include "pi_conv.h"
 
 namespace pu {
-
-typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
-typedef float f4 __attribute__((ext_vector_type(4)));
-
-__device__ __host__ inline float bf2f(uint16_t b) {
-  union {
-    uint32_t u;
-    float f;
-  } v;
-  v.u = (uint32_t)b << 16;
-  return v.f;
-}
-
-// round to nearest even; NaN stays NaN
-__device__ __host__ inline uint16_t f2bf(float f) {
-  union {
-    uint32_t u;
-    float f;
-  } v;
-  v.f = f;
-  if ((v.u & 0x7f800000u) == 0x7f800000u && (v.u & 0x007fffffu)) return (uint16_t)((v.u >> 16) | 0x40);
-  const uint32_t r = v.u + 0x7fffu + ((v.u >> 16) & 1u);
-  return (uint16_t)(r >> 16);
-}
-
-struct Tens {
-  uint16_t *p;
-  int n, d, h, w, c, ld, off;
-};
 
 __host__ inline Tens tens(const pu_tensor *t) {
   return Tens{(uint16_t *)t->ptr, t->n, t->d, t->h, t->w, t->c, t->ld, t->off};
 }
-
-struct ConvP {
-  Tens x, y;
-  const uint16_t *w;
-  const float *bias;
-  int taps, cin, cout;
-  int md, mh, mw, sin, sout, ooz, ooy, oox;
-  int relu, yfp32, acc;
-  int64_t P;
-  int8_t offs[27][3];
-};
 
 __device__ inline void decompose(int64_t p, int md, int mh, int mw, int &nb, int &z, int &y, int &x) {
   x = (int)(p % mw);
@@ -203,16 +164,6 @@ __global__ __launch_bounds__(256) void k_conv(ConvP a) {
       }
 }
 
-struct WgP {
-  Tens x, g;
-  int taps, cin, cout;
-  int md, mh, mw, sin, sout, ooz, ooy, oox;
-  int64_t P, chunk;
-  float *part;   // [nsplit][taps][cin][cout]
-  float *bpart;  // [nsplit][cout] or NULL
-  int8_t offs[27][3];
-};
-
 // Partial weight gradient over one chunk of positions for one (tap, 64-ci,
 // 64-co) tile.
 __global__ __launch_bounds__(256) void k_wgrad(WgP a) {
@@ -300,13 +251,34 @@ __global__ __launch_bounds__(256) void k_wgrad(WgP a) {
   }
 }
 
-// Sum `nsplit` partial arrays of `count` floats in split order.
-__global__ void k_sum_splits(const float *part, int64_t count, int nsplit, float *out) {
-  const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (i >= count) return;
-  float s = 0.f;
-  for (int k = 0; k < nsplit; ++k) s += part[(int64_t)k * count + i];
-  out[i] = s;
+// Sum `nsplit` partial arrays of `count` floats, in a fixed order: a lane
+// takes four consecutive floats of a quarter of the arrays (one quarter per
+// wave, eight loads in flight), and the quarters are added through LDS.
+// Bound by reading the partials: at 256 x 27 x 64 x 32 floats 57 MB.
+constexpr int kSumCols = 64 * 4;  // floats of a workgroup
+__global__ __launch_bounds__(256) void k_sum_splits(const float *part, int64_t count, int nsplit, int vec, float *out) {
+  __shared__ f4 red[3][64];
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  const int64_t i = (int64_t)blockIdx.x * kSumCols + 4 * lane;
+  const int left = i < count ? (int)min((int64_t)4, count - i) : 0;
+  const int k0 = (int)((int64_t)nsplit * wave / 4), k1 = (int)((int64_t)nsplit * (wave + 1) / 4);
+  f4 s = f4{0.f, 0.f, 0.f, 0.f};
+  if (vec && left == 4) {
+#pragma unroll 8
+    for (int k = k0; k < k1; ++k) s += *(const f4 *)(part + (int64_t)k * count + i);
+  } else {
+    for (int k = k0; k < k1; ++k)
+#pragma unroll
+      for (int e = 0; e < 4; ++e)
+        if (e < left) s[e] += part[(int64_t)k * count + i + e];
+  }
+  if (wave) red[wave - 1][lane] = s;
+  __syncthreads();
+  if (wave) return;
+  s = ((s + red[0][lane]) + red[1][lane]) + red[2][lane];
+#pragma unroll
+  for (int e = 0; e < 4; ++e)
+    if (e < left) out[i + e] = s[e];
 }
 
 __global__ void k_transpose_taps(const uint16_t *w, uint16_t *wt, int taps, int cin, int cout) {
@@ -320,13 +292,28 @@ __global__ void k_transpose_taps(const uint16_t *w, uint16_t *wt, int taps, int 
 
 __device__ inline int64_t elem(const Tens &t, int64_t cell, int c) { return cell * t.ld + t.off + c; }
 
+// V channels per lane: eight with 16-byte accesses where both tensors allow
+// them, else one.  Bound by memory: y and g read, g written.
+template <int V>
 __global__ void k_relu_bwd(Tens y, Tens g, int64_t cells) {
   const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (i >= cells * y.c) return;
-  const int64_t cell = i / y.c;
-  const int c = (int)(i % y.c);
-  const int64_t gi = elem(g, cell, c);
-  if (!(bf2f(y.p[elem(y, cell, c)]) > 0.f)) g.p[gi] = 0;
+  const int per = y.c / V;
+  if (i >= cells * per) return;
+  const int64_t cell = i / per;
+  const int c = (int)(i % per) * V;
+  const uint16_t *yp = y.p + elem(y, cell, c);
+  uint16_t *gp = g.p + elem(g, cell, c);
+  if constexpr (V == 8) {
+    uint16_t yv[8], gv[8];
+    *(uint4 *)yv = *(const uint4 *)yp;
+    *(uint4 *)gv = *(const uint4 *)gp;
+#pragma unroll
+    for (int e = 0; e < 8; ++e)
+      if (!(bf2f(yv[e]) > 0.f)) gv[e] = 0;
+    *(uint4 *)gp = *(const uint4 *)gv;
+  } else {
+    if (!(bf2f(*yp) > 0.f)) *gp = 0;
+  }
 }
 
 // y[n, z, y, x, c] = mean of x over the 2x2x2 block
@@ -568,6 +555,11 @@ __global__ void k_upsample(const float *coarse, int nx, int ny, int nz, int f, i
     ((float *)P)[i] = (accumulate ? ((float *)P)[i] : 0.f) + v;
 }
 
+inline void sum_splits(const float *part, int64_t count, int nsplit, float *out, hipStream_t s) {
+  const int vec = count % 4 == 0 && ((uintptr_t)part & 15) == 0;
+  k_sum_splits<<<(unsigned)((count + kSumCols - 1) / kSumCols), dim3(256), 0, s>>>(part, count, nsplit, vec, out);
+}
+
 inline unsigned blocks(int64_t n, int b = 256) { return (unsigned)((n + b - 1) / b); }
 
 inline bool ok_tensor(const pu_tensor *t) {
@@ -615,6 +607,7 @@ extern "C" pi_status pu_conv(const pu_tensor *x, const void *w, int32_t taps, co
   a.P = (int64_t)x->n * md * mh * mw;
   for (int t = 0; t < taps; ++t)
     for (int k = 0; k < 3; ++k) a.offs[t][k] = offs[3 * t + k];
+  if (conv_fast(a, (hipStream_t)stream)) return PU_LAUNCHED;
   // 32 output channels: a 256 x 32 tile wastes no MFMA columns
   if (a.cout <= 32) {
     k_conv<32><<<dim3(blocks(a.P, 256), 1), dim3(256), 0, (hipStream_t)stream>>>(a);
@@ -660,10 +653,10 @@ extern "C" pi_status pu_conv_wgrad(const pu_tensor *x, const pu_tensor *gy, int3
   for (int t = 0; t < taps; ++t)
     for (int k = 0; k < 3; ++k) a.offs[t][k] = offs[3 * t + k];
   const int tiles = ((a.cin + 63) / 64) * ((a.cout + 63) / 64);
-  k_wgrad<<<dim3(tiles, taps, nsplit), dim3(256), 0, s>>>(a);
+  if (!wgrad_fast(a, nsplit, s)) k_wgrad<<<dim3(tiles, taps, nsplit), dim3(256), 0, s>>>(a);
   const int64_t count = (int64_t)taps * a.cin * a.cout;
-  k_sum_splits<<<blocks(count), dim3(256), 0, s>>>(work, count, nsplit, dw);
-  if (db) k_sum_splits<<<blocks(a.cout), dim3(256), 0, s>>>(a.bpart, a.cout, nsplit, db);
+  sum_splits(work, count, nsplit, dw, s);
+  if (db) sum_splits(a.bpart, a.cout, nsplit, db, s);
   return PU_LAUNCHED;
 }
 
@@ -683,7 +676,13 @@ static bool same_grid(const pu_tensor *a, const pu_tensor *b) {
 extern "C" pi_status pu_relu_backward(const pu_tensor *y, const pu_tensor *g, void *stream) {
   if (!ok_tensor(y) || !ok_tensor(g) || !same_grid(y, g) || y->c != g->c) return PI_ERR_INVALID_ARG;
   const int64_t cells = (int64_t)y->n * y->d * y->h * y->w;
-  k_relu_bwd<<<blocks(cells * y->c), dim3(256), 0, (hipStream_t)stream>>>(tens(y), tens(g), cells);
+  auto by8 = [](const pu_tensor *t) {
+    return t->c % 8 == 0 && t->ld % 8 == 0 && t->off % 8 == 0 && ((uintptr_t)t->ptr & 15) == 0;
+  };
+  if (by8(y) && by8(g))
+    k_relu_bwd<8><<<blocks(cells * (y->c / 8)), dim3(256), 0, (hipStream_t)stream>>>(tens(y), tens(g), cells);
+  else
+    k_relu_bwd<1><<<blocks(cells * y->c), dim3(256), 0, (hipStream_t)stream>>>(tens(y), tens(g), cells);
   return PU_LAUNCHED;
 }
 
@@ -723,7 +722,7 @@ extern "C" pi_status pu_head_backward(const pu_tensor *x, const float *w, const 
   const int nch = (int)((cells + chunk - 1) / chunk);
   k_head_bwd_w<<<dim3(nch), dim3(64), 0, s>>>(tens(x), gy, cells, chunk, work);
   float *red = work + (int64_t)nch * (x->c + 1);
-  k_sum_splits<<<1, dim3(256), 0, s>>>(work, x->c + 1, nch, red);
+  sum_splits(work, x->c + 1, nch, red, s);
   if (hipMemcpyAsync(gw, red, x->c * sizeof(float), hipMemcpyDeviceToDevice, s) != hipSuccess ||
       hipMemcpyAsync(gb, red + x->c, sizeof(float), hipMemcpyDeviceToDevice, s) != hipSuccess)
     return PI_ERR_DEVICE;
