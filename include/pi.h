@@ -154,9 +154,10 @@ pi_status pi_set_inner_iters(pi_plan_t plan, int32_t iters);
  * 0 picks 4 when allowed, else 1.  The autotuner sweeps both knobs.
  * Returns PI_ERR_INVALID_ARG for other values.
  * Solves whose vectors fit the registers of the device run on the chip, in
- * one kernel without a tile (CG in the face-crossing scheme: FP32 up to 4 M
- * cells in 2-D and 2 M in 3-D; FP64 up to half of that, without a mask or
- * with PI_FIXED_POINT_CG), while mseg and lane_cells are both 0, the
+ * one kernel without a tile (CG: FP32 up to 4 M cells in 2-D and 2 M in 3-D,
+ * with PI_CELL_CENTERED where the mask has at most some 600 different
+ * neighbourhoods; FP64 up to half of that, with PI_FIXED_POINT_CG or without
+ * a mask and PI_CELL_CENTERED), while mseg and lane_cells are both 0, the
  * default.  A tile asked for here is used: the solve then streams its vectors
  * through memory.  Either way the arithmetic per cell is the same; the FP64
  * sums are added in another order.

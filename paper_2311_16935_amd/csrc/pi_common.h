@@ -44,7 +44,9 @@ constexpr int32_t kNoStop = 1 << 30;
 constexpr int kResBlock = 1024;
 constexpr int kResMaxWg = 256;
 constexpr int kResRing3 = 3;
-constexpr int kResLds = 150 * 1024;
+constexpr int kResLds = 157 * 1024;
+constexpr int kResSpare = 8;        // cells after a cell-centred box's ring
+constexpr int kResMaxPat = 4096;    // distinct ring codes of a cell-centred grid at most (LDS allows fewer)
 constexpr int kResGroup = 16;  // workgroups whose sums are added first where there are more than 64
 constexpr int kResGroups = kResMaxWg / kResGroup;
 
@@ -224,6 +226,11 @@ struct Inst {
   int32_t res_tx, res_ty; // cells of a workgroup's box along x and (3-D) y
   int32_t res_g, res_r;   // ... and along the march axis: res_g groups of lanes, res_r cells per lane
   int32_t res_bx, res_by; // boxes along x, y
+  int32_t res_npat;       // cell-centred: distinct ring codes, 0 (no data) and 1 (all data) among them
+  int32_t res_tab;        // ... LDS offset of their weights
+  const uint16_t *res_pat;// ... number of each cell's
+  const double *res_wt;   // ... [res_npat][8] operator weights
+  const uint8_t *res_has; // ... bit j: neighbour j holds data
   int64_t res_words;      // exchange words of one tag parity: [res_nwg + kResGroups][8] of partial sums,
                           // then [res_nwg][ring cells] of face cells (two words each in FP64)
   uint64_t *res_x;        // both parities

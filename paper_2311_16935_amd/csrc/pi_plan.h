@@ -55,6 +55,9 @@ struct pi_plan_s {
   int32_t res_nwg = 0;             // workgroups of the on-chip solve (0: does not fit; inst.res_nwg: in use)
   pi::BlockEnt *d_tab_res = nullptr;  // on-chip solve: (0, workgroup) for each
   uint64_t *res_x = nullptr;          // ... and its exchange words
+  uint16_t *res_pat = nullptr;        // ... cell-centred: ring code numbers, weights, neighbour bits
+  double *res_wt = nullptr;
+  uint8_t *res_has = nullptr;
   pi::State *h_state = nullptr;    // pinned mirror
   hipGraphExec_t graph = nullptr;  // cached outer-step graph
   int graph_key = -1;

@@ -8,6 +8,7 @@
 #include <algorithm>
 #include <new>
 #include <numeric>
+#include <unordered_map>
 #include <vector>
 
 #include "pi_kernels.h"
@@ -428,6 +429,60 @@ static int32_t components(const pi_plan_s *p, const uint8_t *mask, std::vector<i
   return k;
 }
 
+// Cell-centred plans: number the grid's distinct ring codes (0 no data, 1 all
+// of the ring holds data) and tabulate the inner operator's weights by number,
+// as cc_weights forms them, for the on-chip solve.  res_npat stays 0 where
+// there are too many.
+static pi_status ring_codes(pi_plan_s *p, Inst &in) {
+  const int64_t n = p->ncell;
+  if (n > (int64_t)kResMaxWg * kResBlock * 16) return PI_OK;
+  std::vector<uint32_t> code(n);
+  if (hipMemcpy(code.data(), p->code, n * sizeof(uint32_t), hipMemcpyDeviceToHost) != hipSuccess) return PI_ERR_DEVICE;
+  std::vector<uint32_t> list = {0u, kValidBit | kCcRing};
+  std::unordered_map<uint32_t, uint16_t> num = {{list[0], 0}, {list[1], 1}};
+  std::vector<uint16_t> pat(n);
+  for (int64_t c = 0; c < n; ++c) {
+    if (code[c] == list[1]) {
+      pat[c] = 1;
+      continue;
+    }
+    auto it = num.find(code[c]);
+    if (it == num.end()) {
+      if ((int)list.size() >= kResMaxPat) return PI_OK;
+      it = num.emplace(code[c], (uint16_t)list.size()).first;
+      list.push_back(code[c]);
+    }
+    pat[c] = it->second;
+  }
+  const size_t np = list.size();
+  std::vector<double> wt(np * 8, 0.0);
+  std::vector<uint8_t> has(np, 0);
+  for (size_t i = 1; i < np; ++i) {
+    const uint32_t cd = list[i];
+    for (int j = 0; j < 8; ++j) has[i] |= (uint8_t)(((cd >> cc_bit(cc_dx(j), cc_dy(j))) & 1u) << j);
+    if (in.inner_op) {
+      for (int j = 0; j < 8; ++j) wt[8 * i + j] = (has[i] >> j) & 1 ? in.cc_a[j] : 0.0;
+    } else {
+      cc_pieces([&](int J, int jb, int kb, int maj, int mi) {
+        if (((cd >> jb) & 1u) && ((cd >> kb) & 1u)) wt[8 * i + J] += in.cc_m[maj][mi];
+      });
+    }
+  }
+  if (plan_alloc(p, (void **)&p->res_pat, n * sizeof(uint16_t)) != hipSuccess ||
+      plan_alloc(p, (void **)&p->res_wt, wt.size() * sizeof(double)) != hipSuccess ||
+      plan_alloc(p, (void **)&p->res_has, has.size()) != hipSuccess)
+    return PI_ERR_OOM;
+  if (hipMemcpy(p->res_pat, pat.data(), n * sizeof(uint16_t), hipMemcpyHostToDevice) != hipSuccess ||
+      hipMemcpy(p->res_wt, wt.data(), wt.size() * sizeof(double), hipMemcpyHostToDevice) != hipSuccess ||
+      hipMemcpy(p->res_has, has.data(), has.size(), hipMemcpyHostToDevice) != hipSuccess)
+    return PI_ERR_DEVICE;
+  in.res_npat = (int32_t)np;
+  in.res_pat = p->res_pat;
+  in.res_wt = p->res_wt;
+  in.res_has = p->res_has;
+  return PI_OK;
+}
+
 // (Re)build the single-instance block table and partial-sum slots for the
 // plan's current strip decomposition.
 hipError_t plan_tables(pi_plan_s *p) {
@@ -581,25 +636,6 @@ extern "C" pi_status pi_plan(int ndim, const int64_t dims[3], const double spaci
   in.inner_floor = p->fixed_point ? (p->fp64 ? 1e-26 : 1e-14) : 0.0;
   fill_luts(p, in);
   if (p->cc) fill_cc(p, in);
-  int dev = 0, cus = 0, coop = 0;
-  if (hipGetDevice(&dev) != hipSuccess ||
-      hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess ||
-      hipDeviceGetAttribute(&coop, hipDeviceAttributeCooperativeLaunch, dev) != hipSuccess) {
-    pi_plan_destroy(p);
-    return PI_ERR_DEVICE;
-  }
-  // solved on the chip where it fits.  FP64 solves of the paper's iteration
-  // on grids with missing data stream: rounding grows along their trajectory
-  // (measured on 386 x 301 with 5 % missing: sums in another order, 1e-16
-  // apart, move the 40th iterate by up to 2e-10 and the 60th by 5e-6 of its
-  // norm; without missing data they stay 1e-16 apart), and FP64 callers get
-  // the iterates they always had.  FP32 vectors round such differences away.
-  if (!p->fp64 || !mask || p->fixed_point) set_resident(in, p->fp64, coop ? cus : 1);
-  p->res_nwg = in.res_nwg;
-  if (in.res_nwg > 0 && resident_setup() != hipSuccess) {
-    pi_plan_destroy(p);
-    return PI_ERR_DEVICE;
-  }
   in.ncomp = p->ncomp;
   in.inv_nvalid = 1.0 / (double)nvalid;
 
@@ -621,6 +657,34 @@ extern "C" pi_status pi_plan(int ndim, const int64_t dims[3], const double spaci
   }
   (void)hipFree(d_mask);
   in.code = p->code;
+
+  int dev = 0, cus = 0, coop = 0;
+  if (hipGetDevice(&dev) != hipSuccess ||
+      hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess ||
+      hipDeviceGetAttribute(&coop, hipDeviceAttributeCooperativeLaunch, dev) != hipSuccess) {
+    pi_plan_destroy(p);
+    return PI_ERR_DEVICE;
+  }
+  // solved on the chip where it fits.  FP64 solves of the paper's iteration
+  // stream on grids with missing data and in the cell-centred scheme:
+  // rounding grows along their trajectories (386 x 301, 5 % missing: sums in
+  // another order, 1e-16 apart, move the 40th iterate by up to 2e-10 and the
+  // 60th by 5e-6 of its norm; cell-centred 130 x 91: 6e-11 after 30; the
+  // face-crossing scheme without missing data stays 1e-16 apart), and FP64
+  // callers get the iterates they always had.  FP32 vectors round such
+  // differences away.
+  if (!p->fp64 || p->fixed_point || (!mask && !p->cc)) {
+    if (p->cc && ring_codes(p, in) != PI_OK) {
+      pi_plan_destroy(p);
+      return PI_ERR_OOM;
+    }
+    set_resident(in, p->fp64, coop ? cus : 1);
+  }
+  p->res_nwg = in.res_nwg;
+  if (in.res_nwg > 0 && resident_setup() != hipSuccess) {
+    pi_plan_destroy(p);
+    return PI_ERR_DEVICE;
+  }
 
   if (p->ncomp > 1) {
     std::vector<double> inv(p->ncomp);
@@ -733,7 +797,7 @@ extern "C" void pi_plan_destroy(pi_plan_t p) {
   if (p->graph) (void)hipGraphExecDestroy(p->graph);
   if (p->cap_stream) (void)hipStreamDestroy(p->cap_stream);
   void *ptrs[] = {p->code, p->label, p->comp_inv, p->comp_sum, p->comp_order, p->seg_begin, p->comp_seg,
-                  p->seg_sum, p->P[0], p->P[1], p->S64, p->res, p->q, p->res1, p->d_tab_res, p->res_x,
+                  p->seg_sum, p->P[0], p->P[1], p->S64, p->res, p->q, p->res1, p->d_tab_res, p->res_x, p->res_pat, p->res_wt, p->res_has,
                   p->d, p->p[0], p->bs[0], p->bs[1], p->bs[2], p->bs[3], p->d_inst, p->d_state,
                   p->d_tab, p->d_tab_rq, p->d_part};
   for (void *q : ptrs)

@@ -7,26 +7,32 @@
 
 namespace pi {
 
-// Ring cells of a box: its faces along the march axis, y (3-D) and x.
+// Ring cells of a box: its faces along the march axis, y (3-D) and x, and its
+// corners in the cell-centred scheme.
 __host__ __device__ inline int res_ring(const Inst &in) {
   const int tm = in.res_g * in.res_r;
-  return in.ndim == 3 ? 2 * (in.res_tx * in.res_ty + in.res_tx * tm + in.res_ty * tm) : 2 * (in.res_tx + tm);
+  return in.ndim == 3 ? 2 * (in.res_tx * in.res_ty + in.res_tx * tm + in.res_ty * tm)
+                      : 2 * (in.res_tx + tm) + (in.cc ? 4 : 0);
 }
 
 // LDS bytes of a workgroup: the box and its ring of p followed by q of every
-// lane's cells, or in their place P (FP64) of the box and its ring.
-inline size_t res_lds(const Inst &in, bool fp64) {
+// lane's cells, or in their place P (FP64) of the box and its ring; after them
+// the cell-centred scheme's weights and neighbour bits by ring code.
+inline size_t res_boxes(const Inst &in, bool fp64) {
   const size_t sx = in.res_tx + 2, sy = in.ndim == 3 ? in.res_ty + 2 : 1;
-  const size_t tile = sx * sy * ((size_t)in.res_g * in.res_r + 2), t = fp64 ? 8 : 4;
-  return std::max(tile * sizeof(double), (tile + (size_t)kResBlock * in.res_r) * t);
+  const size_t tile = sx * sy * ((size_t)in.res_g * in.res_r + 2) + (in.cc ? kResSpare : 0), t = fp64 ? 8 : 4;
+  return (std::max(tile * sizeof(double), (tile + (size_t)kResBlock * in.res_r) * t) + 15) / 16 * 16;
+}
+inline size_t res_lds(const Inst &in, bool fp64) {
+  return res_boxes(in, fp64) + (in.cc ? (size_t)in.res_npat * (8 * (fp64 ? 8 : 4) + 1) : 0);
 }
 
 // Microseconds of a pass of the on-chip solve, fitted to boxes of every shape:
 // the cells of a lane (more each where they outgrow the registers), and the
 // exchange -- one hop up to 64 workgroups, two beyond -- longer with the ring
 // words a workgroup reads.
-inline double res_cost(int ndim, int r, int ring, int nwg) {
-  const double cell = (r > 8 ? 0.47 : 0.3) * (ndim == 3 ? 1.3 : 1.0);
+inline double res_cost(const Inst &in, int r, int ring, int nwg) {
+  const double cell = (r > 8 ? 0.47 : 0.3) * (in.ndim == 3 || in.cc ? 1.3 : 1.0);
   const double wait = nwg == 1 ? 0.0 : nwg <= 64 ? 2.05 : 3.0 + 0.004 * nwg;
   return 0.45 + cell * r + wait + (nwg == 1 ? 0.0 : ring * (0.0004 + 0.0006 * nwg / 256.0));
 }
@@ -36,7 +42,7 @@ inline double res_cost(int ndim, int r, int ring, int nwg) {
 // parts.  cus: CUs of the device.
 inline void set_resident(Inst &in, bool fp64, int cus) {
   in.res_nwg = 0;
-  if (in.bicg || in.cc) return;
+  if (in.bicg || (in.cc && in.res_npat == 0)) return;
   const int max_r = in.ndim == 2 ? (fp64 ? 8 : 16) : (fp64 ? 4 : 8);
   const int max_wg = std::min(cus, kResMaxWg);
   if (in.ncell > (int64_t)max_wg * kResBlock * max_r) return;
@@ -54,7 +60,7 @@ inline void set_resident(Inst &in, bool fp64, int cus) {
     const int ring = res_ring(c);
     if (ring > ring_max || res_lds(c, fp64) > (size_t)kResLds) return;
     const int nwg = (int)(bx * by * bm);
-    const double cost = res_cost(in.ndim, r, ring, nwg);
+    const double cost = res_cost(in, r, ring, nwg);
     if (cost >= best) return;
     best = cost;
     in.res_nwg = nwg;
@@ -65,6 +71,7 @@ inline void set_resident(Inst &in, bool fp64, int cus) {
     in.res_r = r;
     in.res_bx = (int)bx;
     in.res_by = (int)by;
+    in.res_tab = (int)res_boxes(c, fp64);
   };
   for (int kx = 1; kx <= in.nx && kx <= max_wg; ++kx) {
     const int tx = (in.nx + kx - 1) / kx;

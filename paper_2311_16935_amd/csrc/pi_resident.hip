@@ -144,7 +144,7 @@ __device__ inline double lane_value(double v, int lane) {
 struct Shared {
   double wred[kRWaves * 4];   // per-wave sums
   double lut[6][kStates];     // operator weights by direction and state (as T)
-  double a[6];                // weights of the fixed point's operator
+  double a[8];                // weights of the fixed point's operator
   double al, be;              // scalars of the next pass
   int end;                    // the inner solve (or, after an outer step, the solve) ends here
   int abort;                  // a wait has lasted kPatience
@@ -241,9 +241,12 @@ __device__ inline bool get_value(PI_G u64 *x, int i, uint32_t tag, T &v) {
 // ---------------------------------------------------------------------------
 // one workgroup's part of a solve: outer steps of about `syncs` synchronisations
 // ---------------------------------------------------------------------------
-// N: cells per lane, HJ: ring cells per lane, OPL: the fixed point's operator.
-template <typename T, int ND, int N, int HJ, bool OPL>
+// SCH: 2, 3 the face-crossing scheme's dimensions, 9 the cell-centred scheme (2-D, nine-point
+// stencils); N: cells per lane, HJ: ring cells per lane, OPL: the fixed point's operator.
+template <typename T, int SCH, int N, int HJ, bool OPL>
 __device__ __forceinline__ void solve_box(const Inst &in, State *gst, int wg, int syncs, Shared &sh, double *dyn) {
+  constexpr int ND = SCH == 3 ? 3 : 2, NB = SCH == 9 ? 8 : 2 * ND;
+  constexpr bool CC = SCH == 9;
   constexpr bool kHold = N <= 4;  // P and S in registers as well
   constexpr int kBits = ND == 3 ? 5 : 3;
   const int t = threadIdx.x, lane = t & 63, wave = __builtin_amdgcn_readfirstlane(t >> 6);
@@ -255,7 +258,8 @@ __device__ __forceinline__ void solve_box(const Inst &in, State *gst, int wg, in
   const int by = ND == 3 ? bq % in.res_by : 0, bm = ND == 3 ? bq / in.res_by : bq;
   const int ox = bx * TX, oy = by * TY, om = bm * TM;
   T *tile = (T *)dyn;                             // p of the box and its ring
-  T *const qbox = tile + (size_t)PS * (TM + 2);   // q of the box, [j][lane]
+  const int spare = CC ? PS * (TM + 2) : 0;       // where lanes without a ring cell write (a corner, unless it is one)
+  T *const qbox = tile + (size_t)PS * (TM + 2) + (CC ? kResSpare : 0);  // q of the box, [j][lane]
   T *const qown = qbox + threadIdx.x;
   double *tileP = dyn;                            // the outer step's P, over both
 
@@ -280,14 +284,18 @@ __device__ __forceinline__ void solve_box(const Inst &in, State *gst, int wg, in
     const uint32_t c = fresh(codes[j / kPack]);
     return kPack == 1 ? c : (c >> (16 * (j & 1))) & 0xffffu;
   };
-  constexpr uint32_t kData = ND == 2 ? 1u << 15 : kValidBit;
-  constexpr uint32_t kInterior = ND == 2 ? (interior_code<2>() & 0xfffu) | kData : interior_code<ND>();
+  // the cell-centred scheme's are numbers of the plan's distinct ring codes:
+  // 0 no data, 1 all of the ring holds data
+  constexpr uint32_t kData = CC ? 0xffffu : ND == 2 ? 1u << 15 : kValidBit;
+  constexpr uint32_t kInterior = CC ? 1u : ND == 2 ? (interior_code<2>() & 0xfffu) | kData : interior_code<ND>();
+  const PI_G uint16_t *gpat = (const PI_G uint16_t *)in.res_pat;
   uint32_t have = 0, usual_rows = 0;
 #pragma unroll
   for (int j = 0; j < N; ++j) {
     const bool e = inxy && j < R && m0 + j < nm;
-    uint32_t cd = e ? gcode[c0 + j * sm] : 0u;
-    if (ND == 2) cd = (cd & 0xfffu) | (cd >> 31 << 15);
+    uint32_t cd = 0u;
+    if (e) cd = CC ? (uint32_t)gpat[c0 + j * sm] : gcode[c0 + j * sm];
+    if (ND == 2 && !CC) cd = (cd & 0xfffu) | (cd >> 31 << 15);
     if (kPack == 1 || (j & 1) == 0) codes[j / kPack] = cd;
     else codes[j / kPack] |= cd << 16;
     if (e) have |= 1u << j;
@@ -313,7 +321,7 @@ __device__ __forceinline__ void solve_box(const Inst &in, State *gst, int wg, in
   // face cells lie in the exchange buffer in the same order, so a ring cell is
   // the word at its place on the opposite face of the box beyond.
   int hw[HJ];          // ring cell: word to read (-1: outside the grid)
-  uint32_t hf[HJ];     // its place in the tile (16 bits; 0, a corner: none), the face cell's in qbox
+  uint32_t hf[HJ];     // its place in the tile (16 bits; `spare`: none), the face cell's in qbox
                        // (14 bits), bit 31: the face cell is wanted
   const int ring0 = (t + kRB - 256) & (kRB - 1);  // first of this lane's ring cells, kRB apart
   const int word0 = wg * res_ring(in) + ring0;
@@ -326,6 +334,7 @@ __device__ __forceinline__ void solve_box(const Inst &in, State *gst, int wg, in
       const int h = ring0 + kRB * i;
       int lx = 0, ly = 0, lm = 0, u, size, stride;
       bool low;
+      const int sides = 2 * (A + B + C);
       if (h < 2 * A) {
         low = h < A;
         u = low ? h : h - A;
@@ -343,6 +352,14 @@ __device__ __forceinline__ void solve_box(const Inst &in, State *gst, int wg, in
         ly = low ? -1 : TY;
         size = B;
         stride = in.res_bx;
+      } else if (CC && h >= sides) {
+        // corners, opposite ones three places apart in sum
+        u = h - sides;
+        low = true;
+        lx = (u & 1) ? TX : -1;
+        lm = (u & 2) ? TM : -1;
+        size = 3 - 2 * u;
+        stride = ((u & 1) ? -1 : 1) + ((u & 2) ? -in.res_bx : in.res_bx);
       } else {
         u = h - 2 * (A + B);
         low = u < C;
@@ -362,7 +379,7 @@ __device__ __forceinline__ void solve_box(const Inst &in, State *gst, int wg, in
       Ph[i] = e ? gP[ox + lx + (oy + ly) * nx + (om + lm) * sm] : 0.0;
       // the box's own cell next to it, wanted where the box beyond exists
       const int fx = min(max(lx, 0), TX - 1), fy = min(max(ly, 0), TY - 1), fm = min(max(lm, 0), TM - 1);
-      const uint32_t at_tile = ok ? (lm + 1) * PS + (ND == 3 ? (ly + 1) * SX : 0) + lx + 1 : 0;
+      const uint32_t at_tile = ok ? (lm + 1) * PS + (ND == 3 ? (ly + 1) * SX : 0) + lx + 1 : spare;
       const uint32_t at_q = ok ? (fm % R) * kRB + fx + TX * (fy + TY * (fm / R)) : 0;
       hf[i] = at_tile | at_q << 16 | (e && in_grid(fx, fy, fm) ? 1u << 31 : 0u);
       rh[i] = ph[i] = dh[i] = T(0);
@@ -370,19 +387,32 @@ __device__ __forceinline__ void solve_box(const Inst &in, State *gst, int wg, in
   }
 
   // weights: [W^{n+1}] from the plan's table, the fixed point's operator
-  // from the face totals; state 0 (no data) has weight 0
+  // from the face totals; state 0 (no data) has weight 0.  Cell-centred: both
+  // by ring code, with a bit per neighbour that holds data.
   T(*lut)[kStates] = (T(*)[kStates])sh.lut;
-  for (int i = t; i < 6 * kStates; i += kRB) {
-    const int d = i / kStates, s = i % kStates;
-    lut[d][s] = OPL ? (s ? (T)in.a[d] : T(0)) : (T)in.lut_np1[d][s];
+  T(*pat)[8] = (T(*)[8])((char *)dyn + in.res_tab);
+  uint8_t *has = (uint8_t *)(pat + in.res_npat);
+  if constexpr (CC) {
+    for (int i = t; i < in.res_npat * 8; i += kRB) pat[i / 8][i % 8] = (T)in.res_wt[i];
+    for (int i = t; i < in.res_npat; i += kRB) has[i] = in.res_has[i];
+    __syncthreads();
+  } else {
+    for (int i = t; i < 6 * kStates; i += kRB) {
+      const int d = i / kStates, s = i % kStates;
+      lut[d][s] = OPL ? (s ? (T)in.a[d] : T(0)) : (T)in.lut_np1[d][s];
+    }
   }
-  T wi[2 * ND];
+  T wi[NB];
 #pragma unroll
-  for (int d = 0; d < 2 * ND; ++d) {
-    const int s = dstate(usual, d, kBits);
-    wi[d] = OPL ? (s ? (T)in.a[d] : T(0)) : (T)in.lut_np1[d][s];
+  for (int d = 0; d < NB; ++d) {
+    if constexpr (CC) {
+      wi[d] = pat[usual][d];
+    } else {
+      const int s = dstate(usual, d, kBits);
+      wi[d] = OPL ? (s ? (T)in.a[d] : T(0)) : (T)in.lut_np1[d][s];
+    }
   }
-  if (t < 6) sh.a[t] = in.a[t];
+  if (t < NB) sh.a[t] = CC ? in.cc_a[t] : in.a[t];
 
   if (t == 0) {
     sh.st = *gst;
@@ -522,22 +552,29 @@ __device__ __forceinline__ void solve_box(const Inst &in, State *gst, int wg, in
       if (j >= fresh_s(R)) continue;
       const int o = io + j * PS;
       const uint32_t cd = code_of(j);
+      double L = 0.0;
       const double vC = tileP[o], vB = tileP[o - PS], vF = tileP[o + PS];
       const double vW = tileP[o - 1], vE = tileP[o + 1];
-      double w[2 * ND];
+      if constexpr (CC) {
+        const uint32_t hb = has[cd];
+        const double nb[8] = {vE, vW, vF, vB, tileP[o + PS + 1], tileP[o + PS - 1], tileP[o - PS + 1], tileP[o - PS - 1]};
 #pragma unroll
-      for (int k = 0; k < 2 * ND; ++k) w[k] = dstate(cd, k, kBits) ? sh.a[k] : 0.0;
-      double L = 0.0;
-      L += w[DE] * (vC - vE);
-      L += w[DW] * (vC - vW);
-      if constexpr (ND == 3) {
-        L += w[DN] * (vC - tileP[o + SX]);
-        L += w[DS] * (vC - tileP[o - SX]);
-        L += w[DF] * (vC - vF);
-        L += w[DB] * (vC - vB);
+        for (int k = 0; k < 8; ++k) L += ((hb >> k) & 1u ? sh.a[k] : 0.0) * (vC - nb[k]);
       } else {
-        L += w[DN] * (vC - vF);
-        L += w[DS] * (vC - vB);
+        double w[2 * ND];
+#pragma unroll
+        for (int k = 0; k < 2 * ND; ++k) w[k] = dstate(cd, k, kBits) ? sh.a[k] : 0.0;
+        L += w[DE] * (vC - vE);
+        L += w[DW] * (vC - vW);
+        if constexpr (ND == 3) {
+          L += w[DN] * (vC - tileP[o + SX]);
+          L += w[DS] * (vC - tileP[o - SX]);
+          L += w[DF] * (vC - vF);
+          L += w[DB] * (vC - vB);
+        } else {
+          L += w[DN] * (vC - vF);
+          L += w[DS] * (vC - vB);
+        }
       }
       double S;
       if constexpr (kHold) S = Sr[j];
@@ -595,41 +632,44 @@ __device__ __forceinline__ void solve_box(const Inst &in, State *gst, int wg, in
         T vF = p[j + 1 < N ? j + 1 : j];
         if (j + 1 == N || j + 1 == fresh_s(R)) vF = tile[o + PS];
         const T vW = tile[o - 1], vE = tile[o + 1];
-        T w[2 * ND];
+        T w[NB];
         if ((rows >> j) & 1u) {
 #pragma unroll
-          for (int n = 0; n < 2 * ND; ++n) w[n] = wi[n];
+          for (int n = 0; n < NB; ++n) w[n] = wi[n];
         } else {
 #pragma unroll
-          for (int n = 0; n < 2 * ND; ++n) w[n] = lut[n][dstate(cd, n, kBits)];
+          for (int n = 0; n < NB; ++n) {
+            if constexpr (CC) w[n] = pat[cd][n];
+            else w[n] = lut[n][dstate(cd, n, kBits)];
+          }
         }
-        T s;
-        if constexpr (OPL) {
-          s = T(0);
-          s += w[DE] * (vC - vE);
-          s += w[DW] * (vC - vW);
-          if constexpr (ND == 3) {
-            s += w[DN] * (vC - tile[o + SX]);
-            s += w[DS] * (vC - tile[o - SX]);
-            s += w[DF] * (vC - vF);
-            s += w[DB] * (vC - vB);
-          } else {
-            s += w[DN] * (vC - vF);
-            s += w[DS] * (vC - vB);
-          }
+        T s = OPL ? T(0) : vC;
+        auto term = [&](int n, T v) {
+          if constexpr (OPL) s += w[n] * (vC - v);
+          else s -= w[n] * v;
+        };
+        if constexpr (CC) {
+          // E, W, N, S, then the diagonals
+          term(0, vE);
+          term(1, vW);
+          term(2, vF);
+          term(3, vB);
+          term(4, tile[o + PS + 1]);
+          term(5, tile[o + PS - 1]);
+          term(6, tile[o - PS + 1]);
+          term(7, tile[o - PS - 1]);
+        } else if constexpr (ND == 3) {
+          term(DE, vE);
+          term(DW, vW);
+          term(DN, tile[o + SX]);
+          term(DS, tile[o - SX]);
+          term(DF, vF);
+          term(DB, vB);
         } else {
-          s = vC;
-          s -= w[DE] * vE;
-          s -= w[DW] * vW;
-          if constexpr (ND == 3) {
-            s -= w[DN] * tile[o + SX];
-            s -= w[DS] * tile[o - SX];
-            s -= w[DF] * vF;
-            s -= w[DB] * vB;
-          } else {
-            s -= w[DN] * vF;
-            s -= w[DS] * vB;
-          }
+          term(DE, vE);
+          term(DW, vW);
+          term(DN, vF);
+          term(DS, vB);
         }
         s = (cd & kData) ? s : T(0);
         if constexpr (kQ) q[j] = s;
@@ -700,7 +740,11 @@ __global__ __launch_bounds__(kRB) void k_resident(const BlockEnt *tab, const Ins
     if (opl) solve_box<T, ND, N, HJ, true>(in, st, e.lb, syncs, sh, dyn);        \
     else solve_box<T, ND, N, HJ, false>(in, st, e.lb, syncs, sh, dyn);           \
   } while (0)
-  if (in.ndim == 2) {
+  if (in.cc) {
+    if (in.res_n == 4) PI_BOX(9, 4, 1);
+    else if (in.res_n == 8) PI_BOX(9, 8, 1);
+    else if constexpr (sizeof(T) == 4) PI_BOX(9, 16, 1);
+  } else if (in.ndim == 2) {
     if (in.res_n == 4) PI_BOX(2, 4, 1);
     else if (in.res_n == 8) PI_BOX(2, 8, 1);
     else if constexpr (sizeof(T) == 4) PI_BOX(2, 16, 1);

@@ -92,3 +92,40 @@ def test_batch_of_on_chip_and_streamed_grids_returns_the_single_solves():
         assert float(Ps[5].abs().max()) > 0 and infos[0]["worklist_rebuilds"] >= 1
     for p in plans:
         p.close()
+
+
+CELL_CASES = [  # dims, mask fraction, fp64, fixed-point variant, outer steps
+    ((64, 64), 0.0, False, False, 30),
+    ((1, 40), 0.0, False, False, 20),
+    ((3, 2), 0.0, False, False, 5),
+    ((101, 97), 0.1, False, False, 30),
+    ((260, 131), 0.1, False, False, 30),
+    ((1025, 517), 0.05, False, False, 12),
+    ((2047, 2040), 0.03, False, False, 3),
+    ((300, 200), 0.1, False, True, 1),
+    ((130, 91), 0.0, True, False, 30),
+    ((600, 500), 0.0, True, False, 8),
+]
+
+
+@pytest.mark.parametrize("dims,frac,fp64,variant,steps", CELL_CASES)
+def test_on_chip_cell_centred_solve_follows_the_streaming_one(dims, frac, fp64, variant, steps):
+    """The nine-point stencils: ring corners from diagonal boxes, and weights by ring code."""
+    import paper_2311_16935_amd as pi
+
+    announce("on chip cell-centred", dims, frac, fp64, variant)
+    w = synth.random_small(93, 2, dims, anisotropic=False, mask_frac=frac)
+    g = [x.to(DEV, torch.float64 if fp64 else torch.float32).contiguous() for x in w.grads]
+    plan = pi.Plan(w.dims, w.spacing, mask=w.mask, fp64=fp64, fixed_point=variant, cell_centered=True)
+    tile = pi.pi_get_tile(plan.handle)
+    chip = plan.solve(g, tol=0.0, max_iter=steps, check=False)
+    pi.pi_set_tile(plan.handle, tile, 0)
+    stream = plan.solve(g, tol=0.0, max_iter=steps, check=False)
+    for k in ("outer_iters", "inner_iters_total", "status", "components"):
+        assert chip.info[k] == stream.info[k], k
+    a, b = torch.nan_to_num(chip.P).double(), torch.nan_to_num(stream.P).double()
+    assert torch.equal(torch.isnan(chip.P), torch.isnan(stream.P))
+    err = float((a - b).abs().max()) / max(float(b.square().mean().sqrt()), 1e-300)
+    print(f"on chip cell-centred {dims}: {err:.2e}")
+    assert err <= (1e-12 if fp64 else 1e-5), err
+    plan.close()
