@@ -46,8 +46,9 @@ BYTES_PER_CELL = {
     "k_cg_step": 4 * 4 + 4 * 4,         # r, q, p, delta in; r', q', p', delta out
 }
 # a plan whose CG passes evaluate q = M p again (pi_get_cg_recompute) moves
-# r, p, delta in and r', p', delta out
-CG_RECOMPUTE_BYTES = 3 * 4 + 3 * 4
+# r, p in and r', p' out, and in every second pass delta and an older p in
+# and delta out; the timed passes are both kinds in turn
+CG_RECOMPUTE_BYTES = (2 * 4 + 2 * 4) + (2 * 4 + 4) // 2
 # the cell-centred kernels always read the 4-byte ring code of each cell
 BYTES_PER_CELL_CC = {k: v + 4 for k, v in BYTES_PER_CELL.items()}
 TIMED = (("k_outer", 0), ("k_cg_step", 1))  # names and pi_time_kernel ids (PI_K_OUTER, PI_K_INNER)

@@ -148,6 +148,16 @@ __host__ __device__ inline int dir_bits(int ndim) { return ndim == 3 ? 5 : 3; }
 
 enum Dir { DE = 0, DW = 1, DN = 2, DS = 3, DF = 4, DB = 5 };
 
+// What CG pass k adds to the correction d: alpha_{k-1} p_{k-1}; nothing; or
+// alpha_{k-2} p_{k-2} and alpha_{k-1} p_{k-1}, in that order (cg_add).
+enum class CgAdd { kOne, kNone, kPair };
+
+// Passes of a solve of `iters` CG iterations that add in pairs: the last pass
+// (iters - 1) adds, and every second one before it; pass 1 has one term only.
+__host__ __device__ constexpr CgAdd cg_add(int k, int iters) {
+  return ((iters - 1 - k) & 1) ? CgAdd::kNone : k >= 2 ? CgAdd::kPair : CgAdd::kOne;
+}
+
 struct BlockEnt {
   int32_t inst;   // -1: padding entry, the block exits at once
   int32_t lb;     // block index inside the instance
@@ -248,6 +258,7 @@ struct State {
   double rr;        // CG: r.r of the current inner residual
   double rr0;       // CG: r.r at the start of the inner solve
   double alpha, beta;
+  double alpha_at[2];// CG: alpha_{k-1} by the parity of k, from pass k - 1's sums (pass k + 1 takes it too)
   double rho, omega;// BiCGStab
   double epsR, epsP;
   double red[4];    // scratch for the last block's results

@@ -40,8 +40,8 @@ hipError_t launch(KernelId k, bool fp64, int shape, const LaunchArgs &la);
 // Inner CG pass k >= 1 without a stored q (k_cg_rq) for
 // one plan that qualifies (Inst.cg_rq): 3-D, no missing data, FP32, four
 // cells per lane, rows of one wave strip or of as many overlapping windows
-// as strips.  opl: the fixed point's operator.
-hipError_t launch_cg_rq(bool opl, const LaunchArgs &la);
+// as strips.  opl: the fixed point's operator (then add is kOne).
+hipError_t launch_cg_rq(bool opl, CgAdd add, const LaunchArgs &la);
 
 // The on-chip solve of grids with res_nwg > 0, in outer steps of about
 // `syncs` synchronisations: tab names (instance, workgroup); coop where some

@@ -885,7 +885,8 @@ template <typename T>
 struct CgPass {
   const PI_G T *rold, *qold, *pold;
   PI_G T *rnew, *qnew, *pnew, *d;
-  T al, be;
+  const PI_G T *pm;  // p_{k-2}, where a pass adds two terms to the correction (kPair)
+  T al, be, al2;     // alpha_{k-1}, beta_k, alpha_{k-2} (with pm)
   bool rd_d, wr_d;
   bool skip;
 };
@@ -902,7 +903,7 @@ __device__ inline CgPass<T> cg_pass(const Inst &in, State *st, const double *par
   // thread of the launch), and this pass decides its own below
   c.skip = st->done != 0 || k >= in.inner_iters || st->stop_at < k || (!in.cg_inline && st->stop_at == k);
   if (c.skip) return c;
-  double al = 0.0, be = 0.0;
+  double al = 0.0, be = 0.0, al2 = 0.0;
   if (k > 0) {
     if (in.cg_inline) {
       double s[4];
@@ -915,9 +916,12 @@ __device__ inline CgPass<T> cg_pass(const Inst &in, State *st, const double *par
       }
       al = cs.al;
       be = cs.be;
+      al2 = st->alpha_at[(k & 1) ^ 1];
+      if (lb == 0 && threadIdx.x == 0) st->alpha_at[k & 1] = al;  // for pass k + 1
     } else {
       al = st->alpha;
       be = st->beta;
+      al2 = st->alpha_at[(k & 1) ^ 1];
     }
   }
   // buffers: pass 0 reads the outer residual (res) only, since p_0 = r_0,
@@ -936,6 +940,10 @@ __device__ inline CgPass<T> cg_pass(const Inst &in, State *st, const double *par
   c.pold = gp<T>(k == 1 && rq_p0_is_r(in) ? in.res : in.p[o]);
   c.pnew = gp<T>(in.p[o ^ 1]);
   c.d = gp<T>(in.d);
+  // p_{k-2}: of the buffers this pass writes, cell by cell after reading
+  // them (pass 2's p_0 is the outer residual, whose buffer takes r_2)
+  c.pm = k == 2 ? c.rnew : c.pnew;
+  c.al2 = (T)al2;
   c.al = (T)al;
   c.be = (T)be;
   c.wr_d = k > 0;
@@ -1074,8 +1082,11 @@ __global__ __launch_bounds__(kBlock) void k_cg_step(const BlockEnt *tab, const I
 // neighbours needs A p_{k-1} there, so p_{k-1} is read within two cells (rows
 // y-2 .. y+2 of plane m, rows y-1 .. y+1 of planes m-1 .. m+1, row y of planes
 // m-2 .. m+2; the rows off the wave's own come from L2) and r_{k-1} within
-// one.  Per cell a pass reads r, p and d and writes r', p' and d: 24 bytes
-// instead of 32.  A p_{k-1} is formed with the operator and operand values
+// one.  Per cell a pass reads r and p and writes r' and p': 16 bytes, and every
+// second one adds two terms to the correction, which takes p_{k-2} and d read
+// and d written: 28.  (Adding one term in each pass is 24 bytes in each; a
+// pass that stores q takes 32.)  p_{k-2} is what the buffer that takes p_k
+// still holds.  A p_{k-1} is formed with the operator and operand values
 // the previous pass used for q_{k-1}, in the same order, so r_k, p_k and the
 // sums are those of the stored-q pass bit for bit.  The first pass of an
 // outer step (k_cg_first) is unchanged.
@@ -1087,6 +1098,15 @@ __global__ __launch_bounds__(kBlock) void k_cg_step(const BlockEnt *tab, const I
 // layers next to the y and march faces, as short wave tasks with per-cell
 // codes and the weight table (rq_bnd_march) in blocks of their own.  One
 // kernel does both (k_cg_rq).
+//
+// Bound: HBM for the passes that add (96.6 us for 28 B/cell at 256^3,
+// 851 us at 500^3: 4.1 TB/s, where a copy reaches 4.7), and nearly so for the
+// others (71.6 us and 566 us for 16 B/cell).  Before, a pass took 105 us and
+// 780 us: 24 B/cell, and a step's inputs, loaded one step ahead, were copied
+// to their place at the step's end, which waited for them.  Per step a wave
+// has about 1200 cycles of arithmetic (the operator at four cells) and two
+// waves share a SIMD, so loads want two steps' notice.  The boundary blocks
+// cost 4-10 us of a pass at 256^3.
 // ---------------------------------------------------------------------------
 
 // Per-direction weights of the operator at a cell of code cd, as apply_m
@@ -1164,6 +1184,28 @@ __device__ inline void rq_code_table(uint32_t *ctab) {
   __syncthreads();
 }
 
+// What a pass adds to the correction, and what it reads for that.
+// c: a wave-uniform cell, xo: the lane's byte offset from it.
+template <int W, CgAdd AD>
+__device__ inline void rq_fetch_d(const CgPass<float> &cg, int64_t c, uint32_t xo, Vec<float, W> &d, Vec<float, W> &pm) {
+  auto ld = [&](const PI_G float *arr) {
+    return ldv_nt<W>((const PI_G float *)((const PI_G char *)(arr + c) + xo), 0);
+  };
+  if (AD != CgAdd::kNone) d = cg.rd_d ? ld(cg.d) : vzero<float, W>();
+  if (AD == CgAdd::kPair) pm = ld(cg.pm);
+}
+template <int W, CgAdd AD>
+__device__ inline Vec<float, W> rq_add_d(const CgPass<float> &cg, const Vec<float, W> &d, const Vec<float, W> &pm,
+                                         const Vec<float, W> &p) {
+  Vec<float, W> v;
+#pragma unroll
+  for (int k = 0; k < W; ++k) {
+    if (AD == CgAdd::kOne) v.e[k] = d.e[k] + cg.al * p.e[k];
+    else if (AD == CgAdd::kPair) v.e[k] = (d.e[k] + cg.al2 * pm.e[k]) + cg.al * p.e[k];
+  }
+  return v;
+}
+
 // The interior planes of a wave: [i0, i1), empty unless the
 // row is at least three rows from both y faces.
 __device__ inline void rq_split(const Walk &wk, int &i0, int &i1) {
@@ -1177,7 +1219,7 @@ __device__ inline void rq_split(const Walk &wk, int &i0, int &i1) {
   }
 }
 
-template <int W, bool OPL>
+template <int W, bool OPL, CgAdd AD>
 __device__ inline void rq_int_march(const Inst &in, const CgPass<float> &cg, const Walk &wk, double (&acc)[4]) {
   using T = float;
   int i0, i1;
@@ -1208,17 +1250,50 @@ __device__ inline void rq_int_march(const Inst &in, const CgPass<float> &cg, con
       for (int k = 0; k < W; ++k) o.e[k] = op_w<T, OPL>(wc[k], v.e[k], w[k], e[k], vN.e[k], vS.e[k], vB.e[k], vF.e[k]);
       return o;
     };
-    const PI_G T *R = cg.rold, *Pp = cg.pold;
+    // The wave's row and planes are scalars, so every load and store takes a
+    // scalar row address and the lane's 32-bit byte offset xo in it.
     const int64_t sm = wk.sm, sy = wk.nx;
-    auto at = [&](int j) { return wk.base + (int64_t)j * sm; };
+    const int row = __builtin_amdgcn_readfirstlane(wk.row);
+    i0 = __builtin_amdgcn_readfirstlane(i0);
+    i1 = __builtin_amdgcn_readfirstlane(i1);
+    const int64_t rb = (int64_t)row * in.srow;
+    const uint32_t xo = (uint32_t)(wk.base - (int64_t)wk.row * in.srow) * (uint32_t)sizeof(T);
+    auto at = [&](int j) { return rb + (int64_t)j * sm; };
+    auto ld = [&](const PI_G T *arr, int64_t c) {
+      return ldv<W>((const PI_G T *)((const PI_G char *)(arr + c) + xo), 0);
+    };
+    const PI_G T *R = cg.rold, *Pp = cg.pold;
     // window at m = i0 (rows y-2 .. y+2 and planes i0-2 .. i0+2 are in the grid)
-    Vec<T, W> P0a = ldv<W>(Pp, at(i0)), P0b = ldv<W>(Pp, at(i0 + 1));
-    Vec<T, W> Pn0 = ldv<W>(Pp, at(i0 - 1) + sy), Pn1 = ldv<W>(Pp, at(i0) + sy);
-    Vec<T, W> Ps0 = ldv<W>(Pp, at(i0 - 1) - sy), Ps1 = ldv<W>(Pp, at(i0) - sy);
+    Vec<T, W> P0a = ld(Pp, at(i0)), P0b = ld(Pp, at(i0 + 1));
+    Vec<T, W> Pn0 = ld(Pp, at(i0 - 1) + sy), Pn1 = ld(Pp, at(i0) + sy);
+    Vec<T, W> Ps0 = ld(Pp, at(i0 - 1) - sy), Ps1 = ld(Pp, at(i0) - sy);
+    // inputs of step m: P(y, m+2), P(y+-1, m+1), P(y+-2, m), R(y, m+1),
+    // R(y+-1, m), and the correction and p_{k-2} at (y, m) as AD needs them
+    struct In {
+      Vec<T, W> p2, pn1, ps1, pnn, pss, ry1, rn, rs, d, pm;
+    };
+    // past the wave's last plane: that plane again (read, never used), so
+    // that the loop has no branch around its loads
+    auto fetch = [&](int m, In &f) {
+      const int mc = min(m, i1 - 1);
+      const int64_t c0 = at(mc), c1 = c0 + sm;
+      f.p2 = ld(Pp, c1 + sm);
+      f.ry1 = ld(R, c1);
+      rq_fetch_d<W, AD>(cg, c0, xo, f.d, f.pm);
+      f.pn1 = ld(Pp, c1 + sy);
+      f.ps1 = ld(Pp, c1 - sy);
+      f.pnn = ld(Pp, c0 + 2 * sy);
+      f.pss = ld(Pp, c0 - 2 * sy);
+      f.rn = ld(R, c0 + sy);
+      f.rs = ld(R, c0 - sy);
+    };
+    In fa, fb, fc;
+    fetch(i0, fa);
+    fetch(i0 + 1, fb);
     Vec<T, W> Um1, U0, rk0;
     {
-      const Vec<T, W> Pm1 = ldv<W>(Pp, at(i0 - 1)), Pm2 = ldv<W>(Pp, at(i0 - 2));
-      const Vec<T, W> Rm1 = ldv<W>(R, at(i0 - 1)), R0 = ldv<W>(R, at(i0));
+      const Vec<T, W> Pm1 = ld(Pp, at(i0 - 1)), Pm2 = ld(Pp, at(i0 - 2));
+      const Vec<T, W> Rm1 = ld(R, at(i0 - 1)), R0 = ld(R, at(i0));
       const Vec<T, W> Am1 = opv(Pm1, Pn0, Ps0, Pm2, P0a);
       const Vec<T, W> A0 = opv(P0a, Pn1, Ps1, Pm1, P0b);
 #pragma unroll
@@ -1228,26 +1303,8 @@ __device__ inline void rq_int_march(const Inst &in, const CgPass<float> &cg, con
         U0.e[k] = rk0.e[k] + be * P0a.e[k];
       }
     }
-    // inputs of step m, fetched during step m - 1
-    struct In {
-      Vec<T, W> p2, pn1, ps1, pnn, pss, ry1, rn, rs, d;  // P(y, m+2), P(y+-1, m+1), P(y+-2, m), R(y, m+1), R(y+-1, m), d(y, m)
-    };
-    auto fetch = [&](int m, In &f) {
-      const int64_t c0 = at(m), c1 = at(m + 1);
-      f.p2 = ldv<W>(Pp, at(m + 2));
-      f.pn1 = ldv<W>(Pp, c1 + sy);
-      f.ps1 = ldv<W>(Pp, c1 - sy);
-      f.pnn = ldv<W>(Pp, c0 + 2 * sy);
-      f.pss = ldv<W>(Pp, c0 - 2 * sy);
-      f.ry1 = ldv<W>(R, c1);
-      f.rn = ldv<W>(R, c0 + sy);
-      f.rs = ldv<W>(R, c0 - sy);
-      f.d = cg.rd_d ? ldv_nt<W>(cg.d, c0) : vzero<T, W>();
-    };
-    In cur, nxt;
-    fetch(i0, cur);
-    for (int m = i0; m < i1; ++m) {
-      if (m + 1 < i1) fetch(m + 1, nxt);  // uniform over the wave
+    auto step = [&](int m, const In &cur, In &far) {
+      fetch(m + 2, far);
       // A p_{k-1} where p_k is needed: (y, m+1), (y+1, m), (y-1, m)
       const Vec<T, W> Ay1 = opv(P0b, cur.pn1, cur.ps1, P0a, cur.p2);
       const Vec<T, W> An = opv(Pn1, cur.pnn, P0a, Pn0, cur.pn1);
@@ -1261,9 +1318,7 @@ __device__ inline void rq_int_march(const Inst &in, const CgPass<float> &cg, con
         Us.e[k] = (cur.rs.e[k] - al * As.e[k]) + be * Ps1.e[k];
       }
       const Vec<T, W> q = opv(U0, Un, Us, Um1, U1);  // q_k = A p_k
-      Vec<T, W> dv;
-#pragma unroll
-      for (int k = 0; k < W; ++k) dv.e[k] = cur.d.e[k] + al * P0a.e[k];
+      const Vec<T, W> dv = rq_add_d<W, AD>(cg, cur.d, cur.pm, P0a);
       if (wk.act) {
 #pragma unroll
         for (int k = 0; k < W; ++k) {
@@ -1273,10 +1328,12 @@ __device__ inline void rq_int_march(const Inst &in, const CgPass<float> &cg, con
           acc[2] += qd * qd;
           acc[3] += r * r;
         }
-        const int64_t c = at(m);
-        stv_nt<W>(cg.pnew, c, U0);
-        stv_nt<W>(cg.rnew, c, rk0);
-        if (cg.wr_d) stv_nt<W>(cg.d, c, dv);
+        auto st = [&](PI_G T *arr, const Vec<T, W> &v) {
+          stv_nt<W>((PI_G T *)((PI_G char *)(arr + at(m)) + xo), 0, v);
+        };
+        st(cg.pnew, U0);
+        st(cg.rnew, rk0);
+        if (AD != CgAdd::kNone) st(cg.d, dv);
       }
       Um1 = U0;
       U0 = U1;
@@ -1287,14 +1344,25 @@ __device__ inline void rq_int_march(const Inst &in, const CgPass<float> &cg, con
       Pn1 = cur.pn1;
       Ps0 = Ps1;
       Ps1 = cur.ps1;
-      cur = nxt;
+    };
+    // Each step issues the loads of the step after next.  Three sets of input
+    // registers in turn, so that none is copied while its loads are in flight
+    // (a copy waits for them): this and the loads' distance of two steps are
+    // what the pass's rate hangs on, since 2 waves per SIMD hide little.
+    int m = i0;
+    for (; m + 3 <= i1; m += 3) {
+      step(m, fa, fc);
+      step(m + 1, fb, fa);
+      step(m + 2, fc, fb);
     }
+    if (m < i1) step(m, fa, fc);
+    if (m + 1 < i1) step(m + 1, fb, fa);
   }
 }
 
 // The boundary layers: planes [a, b) of the wave, every operand and code
 // checked.
-template <int W, bool OPL>
+template <int W, bool OPL, CgAdd AD>
 __device__ inline void rq_bnd_march(const Inst &in, const CgPass<float> &cg, const Walk &wk, const float (*lut)[kStates],
                                     const uint32_t *ctab, const float *wi, const float *a, int a0, int a1,
                                     double (&acc)[4]) {
@@ -1372,10 +1440,9 @@ __device__ inline void rq_bnd_march(const Inst &in, const CgPass<float> &cg, con
     const Vec<T, W> As = opv(codes(m, wk.row - 1), Ps1, P0a, Pss, Ps0, Ps2);
     const Vec<T, W> Us = pk(hS1, ldz(R, c0 + oS1, hS1), As, Ps1, t);
     const Vec<T, W> q = opv(codes(m, wk.row), U0, Un, Us, Um1, U1);
-    const Vec<T, W> d = cg.rd_d ? ldv_nt<W>(cg.d, c0) : z;
-    Vec<T, W> dv;
-#pragma unroll
-    for (int k = 0; k < W; ++k) dv.e[k] = d.e[k] + al * P0a.e[k];
+    Vec<T, W> d, pm;
+    rq_fetch_d<W, AD>(cg, c0, 0, d, pm);
+    const Vec<T, W> dv = rq_add_d<W, AD>(cg, d, pm, P0a);
     if (wk.act) {
 #pragma unroll
       for (int k = 0; k < W; ++k) {
@@ -1387,7 +1454,7 @@ __device__ inline void rq_bnd_march(const Inst &in, const CgPass<float> &cg, con
       }
       stv_nt<W>(cg.pnew, c0, U0);
       stv_nt<W>(cg.rnew, c0, rk0);
-      if (cg.wr_d) stv_nt<W>(cg.d, c0, dv);
+      if (AD != CgAdd::kNone) stv_nt<W>(cg.d, c0, dv);
     }
     Um1 = U0;
     U0 = U1;
@@ -1471,16 +1538,17 @@ __device__ inline Walk rq_iwalk(const Inst &in, int lb) {
 // One CG pass.  Blocks 0 .. nblocks-1 of the instance march the interior
 // planes of their strips and segments; the blocks after them (first in the
 // launch's table, so dispatched first) take one boundary-layer task per wave.
-template <int W, bool OPL>
+template <int W, bool OPL, CgAdd AD>
 __global__ __launch_bounds__(kBlock) void k_cg_rq(const BlockEnt *tab, const Inst *__restrict__ insts,
                                                  State *__restrict__ sts, double *part, int kpass) {
   using T = float;
   PI_PROLOGUE
-  const CgPass<T> cg = cg_pass<T>(in, st, part, e.lb, kpass);
+  CgPass<T> cg = cg_pass<T>(in, st, part, e.lb, kpass);
   if (cg.skip) return;
+  if (AD == CgAdd::kPair) cg.rd_d = kpass > 2;  // pass 2's pair is the first
   double acc[4] = {0.0, 0.0, 0.0, 0.0};
   if (e.lb < in.nblocks) {  // uniform over the block
-    rq_int_march<W, OPL>(in, cg, rq_iwalk<W>(in, e.lb), acc);
+    rq_int_march<W, OPL, AD>(in, cg, rq_iwalk<W>(in, e.lb), acc);
   } else {
     __shared__ T lut[6][kStates];
     __shared__ uint32_t ctab[729];
@@ -1495,7 +1563,7 @@ __global__ __launch_bounds__(kBlock) void k_cg_rq(const BlockEnt *tab, const Ins
     int xs, row, a0, a1;
     const int64_t t = (int64_t)(e.lb - in.nblocks) * kWavesPerBlock + (threadIdx.x >> 6);
     if (rq_task(in, t, xs, row, a0, a1))  // uniform over the wave
-      rq_bnd_march<W, OPL>(in, cg, rq_walk<W>(in, xs, row, a0, a1), lut, ctab, wi, a, a0, a1, acc);
+      rq_bnd_march<W, OPL, AD>(in, cg, rq_walk<W>(in, xs, row, a0, a1), lut, ctab, wi, a, a0, a1, acc);
   }
   publish<4>(in, cg_part(in, part, kpass), e.lb, acc);
 }
@@ -1814,6 +1882,7 @@ __global__ __launch_bounds__(kBlock) void k_finalize(const Inst *__restrict__ in
     case K_CG_STEP: {
       const CgScalars cs = cg_scalars(in, st, s);
       st->alpha = cs.al;
+      st->alpha_at[(kpass + 1) & 1] = cs.al;
       st->beta = cs.be;
       if (cs.stop) st->stop_at = kpass + 1;
       break;
@@ -2403,7 +2472,7 @@ hipError_t launch(KernelId k, bool fp64, int shape, const LaunchArgs &la) {
   return fp64 ? launch_t<double>(k, shape, la) : launch_t<float>(k, shape, la);
 }
 
-hipError_t launch_cg_rq(bool opl, const LaunchArgs &la) {
+hipError_t launch_cg_rq(bool opl, CgAdd add, const LaunchArgs &la) {
   if (la.nblocks <= 0) return hipSuccess;
   const dim3 grid(la.nblocks), block(kBlock);
   const BlockEnt *tab = la.tab;
@@ -2412,9 +2481,13 @@ hipError_t launch_cg_rq(bool opl, const LaunchArgs &la) {
   double *part = la.part;
   hipStream_t s = la.stream;
   if (opl)
-    k_cg_rq<4, true><<<grid, block, 0, s>>>(PI_ARGS, la.iarg);
+    k_cg_rq<4, true, CgAdd::kOne><<<grid, block, 0, s>>>(PI_ARGS, la.iarg);
+  else if (add == CgAdd::kOne)
+    k_cg_rq<4, false, CgAdd::kOne><<<grid, block, 0, s>>>(PI_ARGS, la.iarg);
+  else if (add == CgAdd::kNone)
+    k_cg_rq<4, false, CgAdd::kNone><<<grid, block, 0, s>>>(PI_ARGS, la.iarg);
   else
-    k_cg_rq<4, false><<<grid, block, 0, s>>>(PI_ARGS, la.iarg);
+    k_cg_rq<4, false, CgAdd::kPair><<<grid, block, 0, s>>>(PI_ARGS, la.iarg);
   return hipGetLastError();
 }
 

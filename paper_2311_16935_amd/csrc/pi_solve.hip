@@ -44,6 +44,7 @@ struct Launcher {
   bool cg_finalize = false;  // some instance's CG passes need the finalize kernel
   bool cg_rq = false;        // single plan whose CG passes evaluate q again
   bool cg_rq_opl = false;    // ... with the fixed point's operator
+  int cg_pairs = 0;          // ... adding to the correction in pairs (cg_add): CG iterations per outer step, else 0
   Group rq;                  // ... and the table of its CG passes
   Group grp[kShapes];
 
@@ -59,7 +60,8 @@ struct Launcher {
         // every CG pass over the table with the boundary-layer blocks, so
         // that all of a pass's partial-sum slots are written
         LaunchArgs la{rq.tab, insts, sts, part, rq.ntab, s, iarg, x, y};
-        e = iarg > 0 ? launch_cg_rq(cg_rq_opl, la) : launch(k, fp64, g, la);
+        e = iarg > 0 ? launch_cg_rq(cg_rq_opl, cg_pairs ? cg_add(iarg, cg_pairs) : CgAdd::kOne, la)
+                     : launch(k, fp64, g, la);
       } else {
         LaunchArgs la{grp[g].tab, insts, sts, part, grp[g].ntab, s, iarg, x, y};
         e = launch(k, fp64, g, la);
@@ -258,6 +260,9 @@ Launcher single_launcher(pi_plan_s *p) {
   L.cg_finalize = !p->bicgstab && !p->inst.cg_inline;
   L.cg_rq = p->inst.cg_rq != 0 && p->d_tab_rq != nullptr;
   L.cg_rq_opl = p->inst.inner_op != 0;
+  // every pass of the paper's iteration runs, so it is known which is the
+  // last; the fixed point's inner solve may stop at any pass
+  L.cg_pairs = L.cg_rq && !L.cg_rq_opl && p->inner_iters >= 2 ? p->inner_iters : 0;
   L.rq = Group{p->d_tab_rq, p->ntab_rq};
   L.grp[shape_of(p->ndim, p->inst.vw, p->inst.gen, p->inst.cc)] = Group{p->d_tab, p->ntab};
   return L;
@@ -847,9 +852,8 @@ namespace {
 
 // A mid-solve state for timing single launches: a correction is pending, the
 // search direction is not the first one, no convergence, never reaching the
-// tolerance.  CG pass 2 (reads and writes the correction) and the outer
-// kernel read pass 1's partial sums: alpha = 1e-3 and beta = 1, finite and
-// fixed.
+// tolerance.  The first CG pass timed and the outer kernel read seeded partial
+// sums: alpha = 1e-3 and beta = 1, finite and fixed.
 pi_status timing_state(pi_plan_t p, hipStream_t stream) {
   Inst in = p->inst;
   in.tol = -1.0;
@@ -872,6 +876,8 @@ pi_status timing_state(pi_plan_t p, hipStream_t stream) {
   }
   if (hipMemcpyAsync(p->d_inst, &in, sizeof(Inst), hipMemcpyHostToDevice, stream) != hipSuccess ||
       hipMemcpyAsync(p->d_state, &st, sizeof(State), hipMemcpyHostToDevice, stream) != hipSuccess ||
+      hipMemcpyAsync(p->d_part + (size_t)in.part_stride * 4 + (size_t)in.part_base * 4, slots.data(),
+                     slots.size() * sizeof(double), hipMemcpyHostToDevice, stream) != hipSuccess ||
       hipMemcpyAsync(p->d_part + (size_t)(1 + 1) * in.part_stride * 4 + (size_t)in.part_base * 4, slots.data(),
                      slots.size() * sizeof(double), hipMemcpyHostToDevice, stream) != hipSuccess ||
       hipStreamSynchronize(stream) != hipSuccess)
@@ -902,8 +908,12 @@ out:
   return rc;
 }
 
+// Pass index of the i-th timed later pass: both kinds in turn where the plan
+// adds to its correction in pairs.
+int timed_pass(const Launcher &L, int i) { return L.cg_pairs ? 4 + (i & 1) : 2; }
+
 // Per-pass cost of inner CG pass `kpass` (0: the first of an outer step,
-// which reads only the residual; 2: one of the later passes) as a solve runs
+// which reads only the residual; else the later passes) as a solve runs
 // it: kCgPassesTimed
 // passes, each with its finalize kernel where the tile needs one, captured
 // in a HIP graph as the solve captures them and replayed (back-to-back
@@ -920,7 +930,8 @@ pi_status time_cg_pass(pi_plan_t p, int32_t reps, double *avg_ms, hipStream_t st
   hipGraphExec_t ge = nullptr;
   if (hipStreamBeginCapture(cap, hipStreamCaptureModeThreadLocal) != hipSuccess) return PI_ERR_DEVICE;
   hipError_t e2 = hipSuccess;
-  for (int i = 0; i < kCgPassesTimed && e2 == hipSuccess; ++i) e2 = L.go(K_CG_STEP, cap, kpass, nullptr, nullptr, true);
+  for (int i = 0; i < kCgPassesTimed && e2 == hipSuccess; ++i)
+    e2 = L.go(K_CG_STEP, cap, kpass > 0 ? timed_pass(L, i) : 0, nullptr, nullptr, true);
   hipError_t e = hipStreamEndCapture(cap, &g);
   if (e == hipSuccess && e2 == hipSuccess) e = hipGraphInstantiate(&ge, g, nullptr, nullptr, 0);
   if (g) (void)hipGraphDestroy(g);
@@ -947,8 +958,9 @@ extern "C" pi_status pi_time_kernel(pi_plan_t p, int kernel, int32_t reps, doubl
   if (rc != PI_OK) return rc;
   // the kernel alone: without its finalize the state, and so every launch,
   // stays the same
-  const int kpass = 2;
-  return time_launches(stream, reps, avg_ms, [&] { return L.go(k, stream, kpass, nullptr, nullptr, false); });
+  int i = 0;
+  return time_launches(stream, reps, avg_ms,
+                       [&] { return L.go(k, stream, timed_pass(L, i++), nullptr, nullptr, false); });
 }
 
 // tile cache of pi_autotune: (ndim, nx, ny, nz, fp64, bicgstab) -> (mseg, lane cells, non-temporal outer)
