@@ -12,6 +12,69 @@ __device__ inline int dstate(uint32_t code, int d, int bits) {
   return (int)((code >> (bits * d)) & ((1u << bits) - 1u));
 }
 
+// ---------------------------------------------------------------------------
+// lanes of a wave exchanging values in registers (v_mov with DPP, permlane
+// swaps): a few cycles each, where __shfl goes through LDS (above 100)
+// ---------------------------------------------------------------------------
+struct D2 {
+  double a, b;
+};
+// lanes 0-31 of a with lanes 0-31 of b, and lanes 32-63 of a with lanes 32-63 of b
+__device__ inline D2 swap32(double a, double b) {
+  const auto lo = __builtin_amdgcn_permlane32_swap(__double2loint(a), __double2loint(b), false, false);
+  const auto hi = __builtin_amdgcn_permlane32_swap(__double2hiint(a), __double2hiint(b), false, false);
+  return D2{__hiloint2double(hi[0], lo[0]), __hiloint2double(hi[1], lo[1])};
+}
+// the same between odd and even rows of 16 lanes
+__device__ inline D2 swap16(double a, double b) {
+  const auto lo = __builtin_amdgcn_permlane16_swap(__double2loint(a), __double2loint(b), false, false);
+  const auto hi = __builtin_amdgcn_permlane16_swap(__double2hiint(a), __double2hiint(b), false, false);
+  return D2{__hiloint2double(hi[0], lo[0]), __hiloint2double(hi[1], lo[1])};
+}
+// value of the lane K places back inside the row of 16
+template <int K>
+__device__ inline double ror16(double v) {
+  const int lo = __builtin_amdgcn_update_dpp(0, __double2loint(v), 0x120 + K, 0xf, 0xf, false);
+  const int hi = __builtin_amdgcn_update_dpp(0, __double2hiint(v), 0x120 + K, 0xf, 0xf, false);
+  return __hiloint2double(hi, lo);
+}
+
+// Sum over the wave, in every lane.  Level by level the lanes i and i ^ 32,
+// i ^ 16, ... i ^ 1 are added (once lanes 8 apart agree, the lane 4 back
+// holds what lane i ^ 4 does, and so on down).
+__device__ inline double wave_sum(double v) {
+  const D2 a = swap32(v, v);
+  v = a.a + a.b;
+  const D2 b = swap16(v, v);
+  v = b.a + b.b;
+  v += ror16<8>(v);
+  v += ror16<4>(v);
+  v += ror16<2>(v);
+  v += ror16<1>(v);
+  return v;
+}
+
+// Value of the lane before (after); lane 0 (63) gets `end`.  Every lane of
+// the wave must be active.
+template <int CTRL>
+__device__ inline float lane_shift(float v, float end) {
+  return __int_as_float(__builtin_amdgcn_update_dpp(__float_as_int(end), __float_as_int(v), CTRL, 0xf, 0xf, false));
+}
+template <int CTRL>
+__device__ inline double lane_shift(double v, double end) {
+  const int lo = __builtin_amdgcn_update_dpp(__double2loint(end), __double2loint(v), CTRL, 0xf, 0xf, false);
+  const int hi = __builtin_amdgcn_update_dpp(__double2hiint(end), __double2hiint(v), CTRL, 0xf, 0xf, false);
+  return __hiloint2double(hi, lo);
+}
+template <typename T>
+__device__ inline T lane_before(T v, T end) {
+  return lane_shift<0x138>(v, end);  // wave_shr:1
+}
+template <typename T>
+__device__ inline T lane_after(T v, T end) {
+  return lane_shift<0x130>(v, end);  // wave_shl:1
+}
+
 // Code word of a cell whose face neighbours, their laterals and their far
 // cells all hold data: every direction in its last state.
 template <int ND>

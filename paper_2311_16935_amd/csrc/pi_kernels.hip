@@ -306,10 +306,7 @@ __device__ inline void march(const Walk &wk, Load load, Load1 load1, Aux aux, Bo
       fetch(c + sm, m + 1, nxt);
     else
       nxt.v = m + 1 < wk.nm ? load(c + sm) : vzero<V, W>();
-    V left = __shfl_up(cur.v.e[W - 1], 1, kWave);
-    V right = __shfl_down(cur.v.e[0], 1, kWave);
-    if (lane == 0) left = cur.vEdge;
-    if (lane == kWave - 1) right = cur.vEdge;
+    const V left = lane_before(cur.v.e[W - 1], cur.vEdge), right = lane_after(cur.v.e[0], cur.vEdge);
     // lanes past the grid only serve the shuffles: they neither compute
     // (their cells duplicate a neighbour's, which would enter the sums) nor store
     if (wk.act) {
@@ -424,10 +421,7 @@ __device__ inline void march2(const Walk &wk, Load load, Load1 load1, Extra extr
   for (int m = wk.m0; m < wk.m1; ++m, c += sm) {
     fetch(m + 2, ra);
     cook(m + 1, rb, nxt);
-    V left = __shfl_up(cur.v.e[W - 1], 1, kWave);
-    V right = __shfl_down(cur.v.e[0], 1, kWave);
-    if (lane == 0) left = cur.vEdge;
-    if (lane == kWave - 1) right = cur.vEdge;
+    const V left = lane_before(cur.v.e[W - 1], cur.vEdge), right = lane_after(cur.v.e[0], cur.vEdge);
     if (wk.act) {
       Out o[W];
 #pragma unroll
@@ -488,10 +482,7 @@ template <int K>
 __device__ inline void block_sum(double (&v)[K], double *lds) {
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
 #pragma unroll
-  for (int k = 0; k < K; ++k) {
-#pragma unroll
-    for (int o = 32; o > 0; o >>= 1) v[k] += __shfl_xor(v[k], o, kWave);
-  }
+  for (int k = 0; k < K; ++k) v[k] = wave_sum(v[k]);
   __syncthreads();
   if (lane == 0) {
 #pragma unroll
@@ -1150,11 +1141,8 @@ __device__ inline T op_w(const T (&w)[6], T vC, T vW, T vE, T vN, T vS, T vB, T 
 // face where the window ends at one, else a cell the window does not own
 // (rq_window keeps owned cells far enough inside)
 template <typename T, int W>
-__device__ inline void xnb0(const Vec<T, W> &v, int lane, T (&vW)[W], T (&vE)[W]) {
-  T left = __shfl_up(v.e[W - 1], 1, kWave);
-  T right = __shfl_down(v.e[0], 1, kWave);
-  if (lane == 0) left = T(0);
-  if (lane == kWave - 1) right = T(0);
+__device__ inline void xnb0(const Vec<T, W> &v, T (&vW)[W], T (&vE)[W]) {
+  const T left = lane_before(v.e[W - 1], T(0)), right = lane_after(v.e[0], T(0));
 #pragma unroll
   for (int k = 0; k < W; ++k) {
     vW[k] = k == 0 ? left : v.e[k > 0 ? k - 1 : 0];
@@ -1225,7 +1213,6 @@ __device__ inline void rq_int_march(const Inst &in, const CgPass<float> &cg, con
   int i0, i1;
   rq_split(wk, i0, i1);
   if (i0 < i1) {  // uniform over the wave
-    const int lane = threadIdx.x & 63;
     const T al = cg.al, be = cg.be;
     // weights of this lane's cells: their codes depend on x alone here
     T wc[W][6];
@@ -1244,7 +1231,7 @@ __device__ inline void rq_int_march(const Inst &in, const CgPass<float> &cg, con
     auto opv = [&](const Vec<T, W> &v, const Vec<T, W> &vN, const Vec<T, W> &vS, const Vec<T, W> &vB,
                    const Vec<T, W> &vF) {
       T w[W], e[W];
-      xnb0<T, W>(v, lane, w, e);
+      xnb0<T, W>(v, w, e);
       Vec<T, W> o;
 #pragma unroll
       for (int k = 0; k < W; ++k) o.e[k] = op_w<T, OPL>(wc[k], v.e[k], w[k], e[k], vN.e[k], vS.e[k], vB.e[k], vF.e[k]);
@@ -1368,7 +1355,6 @@ __device__ inline void rq_bnd_march(const Inst &in, const CgPass<float> &cg, con
                                     double (&acc)[4]) {
   using T = float;
   if (a0 >= a1) return;  // uniform over the wave
-  const int lane = threadIdx.x & 63;
   const T al = cg.al, be = cg.be;
   const int nm = wk.nm;
   const int64_t sm = wk.sm, sy = wk.nx;
@@ -1396,7 +1382,7 @@ __device__ inline void rq_bnd_march(const Inst &in, const CgPass<float> &cg, con
   auto opv = [&](const Vec<uint32_t, W> &cd, const Vec<T, W> &v, const Vec<T, W> &vN, const Vec<T, W> &vS,
                  const Vec<T, W> &vB, const Vec<T, W> &vF) {
     T w[W], e[W];
-    xnb0<T, W>(v, lane, w, e);
+    xnb0<T, W>(v, w, e);
     Vec<T, W> o;
 #pragma unroll
     for (int k = 0; k < W; ++k) {
@@ -2072,11 +2058,8 @@ struct CcRow {
 // merge into one store to a lane-chosen address, which puts the values in
 // scratch memory.
 template <int W, typename V>
-__device__ inline void cc_sides(const CcRow<W, V> &r, int lane, V (&l)[W], V (&rt)[W]) {
-  const V up = __shfl_up(r.v.e[W - 1], 1, kWave);
-  const V dn = __shfl_down(r.v.e[0], 1, kWave);
-  const V l0 = lane == 0 ? r.edge : up;
-  const V rw = lane == kWave - 1 ? r.edge : dn;
+__device__ inline void cc_sides(const CcRow<W, V> &r, V (&l)[W], V (&rt)[W]) {
+  const V l0 = lane_before(r.v.e[W - 1], r.edge), rw = lane_after(r.v.e[0], r.edge);
 #pragma unroll
   for (int k = 0; k < W; ++k) {
     l[k] = k == 0 ? l0 : r.v.e[k > 0 ? k - 1 : 0];
@@ -2127,9 +2110,9 @@ __device__ inline void march_cc(const Walk &wk, Load load, Load1 load1, Aux aux,
       axn = aux(c + sm);
     }
     V lp[W], rp[W], lc[W], rc[W], ln[W], rn[W];
-    cc_sides<W, V>(prev, lane, lp, rp);
-    cc_sides<W, V>(cur, lane, lc, rc);
-    cc_sides<W, V>(nxt, lane, ln, rn);
+    cc_sides<W, V>(prev, lp, rp);
+    cc_sides<W, V>(cur, lc, rc);
+    cc_sides<W, V>(nxt, ln, rn);
     // lanes past the grid only serve the shuffles
     if (wk.act) {
       Out o[W];

@@ -88,29 +88,6 @@ struct Wait {
 // ---------------------------------------------------------------------------
 // sums
 // ---------------------------------------------------------------------------
-struct D2 {
-  double a, b;
-};
-// lanes 0-31 of a with lanes 0-31 of b, and lanes 32-63 of a with lanes 32-63 of b
-__device__ inline D2 swap32(double a, double b) {
-  const auto lo = __builtin_amdgcn_permlane32_swap(__double2loint(a), __double2loint(b), false, false);
-  const auto hi = __builtin_amdgcn_permlane32_swap(__double2hiint(a), __double2hiint(b), false, false);
-  return D2{__hiloint2double(hi[0], lo[0]), __hiloint2double(hi[1], lo[1])};
-}
-// the same between odd and even rows of 16 lanes
-__device__ inline D2 swap16(double a, double b) {
-  const auto lo = __builtin_amdgcn_permlane16_swap(__double2loint(a), __double2loint(b), false, false);
-  const auto hi = __builtin_amdgcn_permlane16_swap(__double2hiint(a), __double2hiint(b), false, false);
-  return D2{__hiloint2double(hi[0], lo[0]), __hiloint2double(hi[1], lo[1])};
-}
-// value of the lane K places back inside the row of 16
-template <int K>
-__device__ inline double ror16(double v) {
-  const int lo = __builtin_amdgcn_update_dpp(0, __double2loint(v), 0x120 + K, 0xf, 0xf, false);
-  const int hi = __builtin_amdgcn_update_dpp(0, __double2hiint(v), 0x120 + K, 0xf, 0xf, false);
-  return __hiloint2double(hi, lo);
-}
-
 // Sums of four values over a wave.  The first two levels fold the four
 // values into one (each lane group keeps one of them), so that seven adds do
 // instead of 24.  Row of lanes 0-15 gets sum 0, 16-31 sum 2, 32-47 sum 1, 48-63 sum 3.
