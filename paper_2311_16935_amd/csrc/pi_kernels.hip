@@ -306,7 +306,19 @@ __device__ inline void march(const Walk &wk, Load load, Load1 load1, Aux aux, Bo
       fetch(c + sm, m + 1, nxt);
     else
       nxt.v = m + 1 < wk.nm ? load(c + sm) : vzero<V, W>();
-    const V left = lane_before(cur.v.e[W - 1], cur.vEdge), right = lane_after(cur.v.e[0], cur.vEdge);
+    // 3-D: through LDS, whose latency passes while the next plane's loads are
+    // under way; with register moves the compiler orders the loop so that the
+    // CG pass at 200x190x180 with missing data takes 60.7 us instead of 55.1
+    V left, right;
+    if constexpr (ND == 3) {
+      left = __shfl_up(cur.v.e[W - 1], 1, kWave);
+      right = __shfl_down(cur.v.e[0], 1, kWave);
+      if (lane == 0) left = cur.vEdge;
+      if (lane == kWave - 1) right = cur.vEdge;
+    } else {
+      left = lane_before(cur.v.e[W - 1], cur.vEdge);
+      right = lane_after(cur.v.e[0], cur.vEdge);
+    }
     // lanes past the grid only serve the shuffles: they neither compute
     // (their cells duplicate a neighbour's, which would enter the sums) nor store
     if (wk.act) {
