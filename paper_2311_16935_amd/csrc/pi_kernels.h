@@ -37,7 +37,8 @@ struct LaunchArgs {
 
 hipError_t launch(KernelId k, bool fp64, int shape, const LaunchArgs &la);
 
-// Inner CG pass k >= 1 without a stored q (k_cg_rq) for
+// Inner CG pass k without a stored q (k_cg_rq; pass 0, k_cg_rq_first, of the
+// paper's iteration with at least two passes only) for
 // one plan that qualifies (Inst.cg_rq): 3-D, no missing data, FP32, four
 // cells per lane, rows of one wave strip or of as many overlapping windows
 // as strips.  opl: the fixed point's operator (then add is kOne).

@@ -1041,7 +1041,6 @@ __device__ __forceinline__ void cg_step_body(const BlockEnt *tab, const Inst *__
       for (int k = 0; k < W; ++k) x.e[k] = Aux{r.e[k], T(0)};
       return x;
     };
-    const bool keep = !rq_p0_is_r(in);  // uniform over the launch
     auto store0 = [&](int64_t c, const Out (&o)[W]) {
       Vec<T, W> pv, qv;
 #pragma unroll
@@ -1049,10 +1048,8 @@ __device__ __forceinline__ void cg_step_body(const BlockEnt *tab, const Inst *__
         pv.e[k] = o[k].p;
         qv.e[k] = o[k].q;
       }
-      if (keep) {
-        stv_nt<W>(cg.pnew, c, pv);
-        stv_nt<W>(cg.qnew, c, qv);
-      }
+      stv_nt<W>(cg.pnew, c, pv);
+      stv_nt<W>(cg.qnew, c, qv);
     };
     march2<ND, W, GEN, T, Aux, Out>(wk, load0, load01, extra0, cookv0, cook10, cooka0, body, store0);
   } else {
@@ -1466,6 +1463,109 @@ __device__ inline void rq_bnd_march(const Inst &in, const CgPass<float> &cg, con
   }
 }
 
+// Pass 0 of an outer step of the paper's iteration: p_0 = r_0, pass 1 takes
+// it from the residual, and q is evaluated again, so this pass reads r, forms
+// its four sums (p.q and r.q are one) and writes nothing.  The same rows and
+// planes as rq_int_march / rq_bnd_march.  27.8 us at 256^3 in 64-plane segments
+// and 157 us at 500^3 for 4 B/cell; the general first pass, which takes its
+// weights from the table by each cell's code, 57 and 190 us: with one wave
+// per SIMD its arithmetic was the bound.
+template <int W>
+__device__ inline void rq_first_int(const Inst &in, const PI_G float *R, const Walk &wk, double (&acc)[4]) {
+  using T = float;
+  int i0, i1;
+  rq_split(wk, i0, i1);
+  if (i0 >= i1) return;  // uniform over the wave
+  T wc[W][6];
+  {
+    T wi[6];
+#pragma unroll
+    for (int d = 0; d < 6; ++d) wi[d] = (T)in.lut_np1[d][interior_state<3>()];
+    auto lut = [&](int d, int st) { return (T)in.lut_np1[d][st]; };
+#pragma unroll
+    for (int k = 0; k < W; ++k)
+      op_weights<T, false>(lut, wi, wi, code_at<3>(min(wk.x + k, wk.nx - 1), 3, 3, wk.nx, wk.ny, wk.nz), wc[k]);
+  }
+  const int64_t sm = wk.sm, sy = wk.nx;
+  const int row = __builtin_amdgcn_readfirstlane(wk.row);
+  i0 = __builtin_amdgcn_readfirstlane(i0);
+  i1 = __builtin_amdgcn_readfirstlane(i1);
+  const int64_t rb = (int64_t)row * in.srow;
+  const uint32_t xo = (uint32_t)(wk.base - (int64_t)wk.row * in.srow) * (uint32_t)sizeof(T);
+  auto ld = [&](int64_t c) { return ldv<W>((const PI_G T *)((const PI_G char *)(R + c) + xo), 0); };
+  struct In {
+    Vec<T, W> f, n, s;  // r at (y, m+1), (y+1, m), (y-1, m)
+  };
+  auto fetch = [&](int m, In &v) {
+    const int64_t c = rb + (int64_t)min(m, i1 - 1) * sm;
+    v.f = ld(c + sm);
+    v.n = ld(c + sy);
+    v.s = ld(c - sy);
+  };
+  // a step is short (100 operations a lane), so loads are four steps ahead
+  constexpr int kAhead = 4;
+  In v[kAhead + 1];
+  Vec<T, W> b = ld(rb + (int64_t)(i0 - 1) * sm), c = ld(rb + (int64_t)i0 * sm);
+#pragma unroll
+  for (int j = 0; j < kAhead; ++j) fetch(i0 + j, v[j]);
+  for (int m = i0; m < i1; m += kAhead + 1) {
+#pragma unroll
+    for (int j = 0; j <= kAhead; ++j) {
+      if (m + j < i1) {  // uniform over the wave
+        fetch(m + j + kAhead, v[(j + kAhead) % (kAhead + 1)]);
+        const In &u = v[j];
+        T w[W], e[W];
+        xnb0<T, W>(c, w, e);
+#pragma unroll
+        for (int k = 0; k < W; ++k) {
+          const double q =
+              (double)op_w<T, false>(wc[k], c.e[k], w[k], e[k], u.n.e[k], u.s.e[k], b.e[k], u.f.e[k]);
+          const double r = (double)c.e[k];
+          acc[0] += wk.act ? r * q : 0.0;
+          acc[2] += wk.act ? q * q : 0.0;
+          acc[3] += wk.act ? r * r : 0.0;
+        }
+        b = c;
+        c = u.f;
+      }
+    }
+  }
+  acc[1] = acc[0];
+}
+
+template <int W>
+__device__ inline void rq_first_bnd(const PI_G float *R, const Walk &wk, const float (*lut)[kStates],
+                                    const uint32_t *ctab, const float *wi, int a0, int a1, double (&acc)[4]) {
+  using T = float;
+  const int nm = wk.nm;
+  const int64_t sm = wk.sm, sy = wk.nx;
+  const bool hN = wk.row + 1 < wk.ny, hS = wk.row > 0;
+  const Vec<T, W> z = vzero<T, W>();
+  auto at = [&](int j, int64_t off, bool ok) {
+    const Vec<T, W> v = ldv<W>(R, wk.base + (int64_t)min(max(j, 0), nm - 1) * sm + (ok ? off : 0));
+    return ok && j >= 0 && j < nm ? v : z;
+  };
+  auto tl = [&](int d, int st) { return lut[d][st]; };
+  const int cy = 9 * rq_cls(wk.row, wk.ny);
+  for (int m = a0; m < a1; ++m) {
+    const Vec<T, W> c = at(m, 0, true), b = at(m - 1, 0, true), f = at(m + 1, 0, true), n = at(m, sy, hN),
+                    s = at(m, -sy, hS);
+    T w[W], e[W];
+    xnb0<T, W>(c, w, e);
+#pragma unroll
+    for (int k = 0; k < W; ++k) {
+      T wt[6];
+      op_weights<T, false>(tl, wi, wi, ctab[rq_cls(min(wk.x + k, wk.nx - 1), wk.nx) + cy + 81 * rq_cls(m, nm)], wt);
+      const double q = (double)op_w<T, false>(wt, c.e[k], w[k], e[k], n.e[k], s.e[k], b.e[k], f.e[k]);
+      const double r = (double)c.e[k];
+      acc[0] += wk.act ? r * q : 0.0;
+      acc[2] += wk.act ? q * q : 0.0;
+      acc[3] += wk.act ? r * r : 0.0;
+    }
+  }
+  acc[1] = acc[0];
+}
+
 // Boundary-layer task t (rq_ntasks of them) -> wave strip, row and planes
 // [a, b): the rows next to the y faces in chunks of kRqChunk planes, then for
 // every other row the three planes next to each march face; false past the
@@ -1564,6 +1664,33 @@ __global__ __launch_bounds__(kBlock) void k_cg_rq(const BlockEnt *tab, const Ins
       rq_bnd_march<W, OPL, AD>(in, cg, rq_walk<W>(in, xs, row, a0, a1), lut, ctab, wi, a, a0, a1, acc);
   }
   publish<4>(in, cg_part(in, part, kpass), e.lb, acc);
+}
+
+// Pass 0 over the same table and slots.
+template <int W>
+__global__ __launch_bounds__(kBlock) void k_cg_rq_first(const BlockEnt *tab, const Inst *__restrict__ insts,
+                                                       State *__restrict__ sts, double *part) {
+  using T = float;
+  PI_PROLOGUE
+  if (st->done != 0) return;
+  const PI_G T *R = gp<T>((const void *)in.res);
+  double acc[4] = {0.0, 0.0, 0.0, 0.0};
+  if (e.lb < in.nblocks) {  // uniform over the block
+    rq_first_int<W>(in, R, rq_iwalk<W>(in, e.lb), acc);
+  } else {
+    __shared__ T lut[6][kStates];
+    __shared__ uint32_t ctab[729];
+    load_lut<T>(in.lut_np1, lut);
+    rq_code_table(ctab);
+    T wi[6];
+#pragma unroll
+    for (int d = 0; d < 6; ++d) wi[d] = (T)in.lut_np1[d][interior_state<3>()];
+    int xs, row, a0, a1;
+    const int64_t t = (int64_t)(e.lb - in.nblocks) * kWavesPerBlock + (threadIdx.x >> 6);
+    if (rq_task(in, t, xs, row, a0, a1))  // uniform over the wave
+      rq_first_bnd<W>(R, rq_walk<W>(in, xs, row, a0, a1), lut, ctab, wi, a0, a1, acc);
+  }
+  publish<4>(in, cg_part(in, part, 0), e.lb, acc);
 }
 
 // ---------------------------------------------------------------------------
@@ -2475,7 +2602,9 @@ hipError_t launch_cg_rq(bool opl, CgAdd add, const LaunchArgs &la) {
   State *sts = la.sts;
   double *part = la.part;
   hipStream_t s = la.stream;
-  if (opl)
+  if (la.iarg == 0)
+    k_cg_rq_first<4><<<grid, block, 0, s>>>(PI_ARGS);
+  else if (opl)
     k_cg_rq<4, true, CgAdd::kOne><<<grid, block, 0, s>>>(PI_ARGS, la.iarg);
   else if (add == CgAdd::kOne)
     k_cg_rq<4, false, CgAdd::kOne><<<grid, block, 0, s>>>(PI_ARGS, la.iarg);

@@ -60,8 +60,8 @@ struct Launcher {
         // every CG pass over the table with the boundary-layer blocks, so
         // that all of a pass's partial-sum slots are written
         LaunchArgs la{rq.tab, insts, sts, part, rq.ntab, s, iarg, x, y};
-        e = iarg > 0 ? launch_cg_rq(cg_rq_opl, cg_pairs ? cg_add(iarg, cg_pairs) : CgAdd::kOne, la)
-                     : launch(k, fp64, g, la);
+        e = iarg > 0 || cg_pairs ? launch_cg_rq(cg_rq_opl, cg_pairs ? cg_add(iarg, cg_pairs) : CgAdd::kOne, la)
+                                 : launch(k, fp64, g, la);
       } else {
         LaunchArgs la{grp[g].tab, insts, sts, part, grp[g].ntab, s, iarg, x, y};
         e = launch(k, fp64, g, la);

@@ -11,7 +11,7 @@ the size of the term.
 
 Iteration counts: both parities, one pass (no pair), the first pair alone.
 Segments of one, two, three and more planes per wave, short of and past the
-loop's three register sets; few blocks (every block sums the partials) and
+loop's three register sets (pass 0's five); few blocks (every block sums the partials) and
 more than 1024 (finalize kernel); rows of one and of two windows."""
 
 import pytest
