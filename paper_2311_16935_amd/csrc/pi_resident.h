@@ -21,7 +21,8 @@ __host__ __device__ inline int res_ring(const Inst &in) {
 inline size_t res_boxes(const Inst &in, bool fp64) {
   const size_t sx = in.res_tx + 2, sy = in.ndim == 3 ? in.res_ty + 2 : 1;
   const size_t tile = sx * sy * ((size_t)in.res_g * in.res_r + 2) + (in.cc ? kResSpare : 0), t = fp64 ? 8 : 4;
-  return (std::max(tile * sizeof(double), (tile + (size_t)kResBlock * in.res_r) * t) + 15) / 16 * 16;
+  const size_t b = std::max(tile * sizeof(double), (tile + (size_t)kResBlock * in.res_r) * t);
+  return in.cc ? (b + 15) / 16 * 16 : b;
 }
 inline size_t res_lds(const Inst &in, bool fp64) {
   return res_boxes(in, fp64) + (in.cc ? (size_t)in.res_npat * (8 * (fp64 ? 8 : 4) + 1) : 0);
