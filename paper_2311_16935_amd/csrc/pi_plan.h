@@ -25,8 +25,9 @@ struct pi_plan_s {
   double Atot = 0;
   double face[3] = {};      // per-face ray totals by axis
   size_t bytes = 0;         // device bytes held
+  std::vector<void *> owned;  // every plan_alloc, freed by pi_plan_destroy
 
-  // device arrays owned by the plan
+  // device arrays of the plan (d_tab, d_tab_rq and d_part are plan_tables')
   uint32_t *code = nullptr;
   int32_t *label = nullptr;
   double *comp_inv = nullptr;
@@ -66,7 +67,7 @@ struct pi_plan_s {
 
 namespace pi {
 
-// Allocation helper that records the bytes held by the plan.
+// Device memory that lives as long as the plan: recorded in owned and bytes.
 hipError_t plan_alloc(pi_plan_s *p, void **ptr, size_t bytes);
 
 // Geometry of the strip decomposition for one grid (fields of Inst).

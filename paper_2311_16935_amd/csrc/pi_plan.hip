@@ -370,8 +370,12 @@ std::vector<BlockEnt> build_table(const std::vector<Inst *> &insts, int part_bas
 hipError_t plan_alloc(pi_plan_s *p, void **ptr, size_t bytes) {
   *ptr = nullptr;
   if (bytes == 0) return hipSuccess;
+  p->owned.reserve(p->owned.size() + 1);
   hipError_t e = hipMalloc(ptr, bytes);
-  if (e == hipSuccess) p->bytes += bytes;
+  if (e == hipSuccess) {
+    p->owned.push_back(*ptr);
+    p->bytes += bytes;
+  }
   return e;
 }
 
@@ -796,11 +800,8 @@ extern "C" void pi_plan_destroy(pi_plan_t p) {
   if (!p) return;
   if (p->graph) (void)hipGraphExecDestroy(p->graph);
   if (p->cap_stream) (void)hipStreamDestroy(p->cap_stream);
-  void *ptrs[] = {p->code, p->label, p->comp_inv, p->comp_sum, p->comp_order, p->seg_begin, p->comp_seg,
-                  p->seg_sum, p->P[0], p->P[1], p->S64, p->res, p->q, p->res1, p->d_tab_res, p->res_x, p->res_pat, p->res_wt, p->res_has,
-                  p->d, p->p[0], p->bs[0], p->bs[1], p->bs[2], p->bs[3], p->d_inst, p->d_state,
-                  p->d_tab, p->d_tab_rq, p->d_part};
-  for (void *q : ptrs)
+  for (void *q : p->owned) (void)hipFree(q);
+  for (void *q : {(void *)p->d_tab, (void *)p->d_tab_rq, (void *)p->d_part})
     if (q) (void)hipFree(q);
   if (p->h_state) (void)hipHostFree(p->h_state);
   delete p;
