@@ -44,13 +44,28 @@ inline Boxes boxes_of(int n, int d, int h, int w, int bz, int by, int bx) {
   b.count = n * b.tx * b.ty * b.tz;
   return b;
 }
-__device__ inline void box_at(const Boxes &b, int i, int &n, int &z, int &y, int &x) {
-  x = i % b.tx;
+struct BoxAt {
+  int n, z, y, x;
+};
+__device__ inline BoxAt box_at(const Boxes &b, int i) {
+  BoxAt c;
+  c.x = i % b.tx;
   i /= b.tx;
-  y = i % b.ty;
+  c.y = i % b.ty;
   i /= b.ty;
-  z = i % b.tz;
-  n = i / b.tz;
+  c.z = i % b.tz;
+  c.n = i / b.tz;
+  return c;
+}
+__device__ inline BoxAt box_after(const Boxes &b, BoxAt c) {
+  if (++c.x < b.tx) return c;
+  c.x = 0;
+  if (++c.y < b.ty) return c;
+  c.y = 0;
+  if (++c.z < b.tz) return c;
+  c.z = 0;
+  ++c.n;
+  return c;
 }
 
 // index in the caller's tap list of the tap (dz, dy, dx) in {-1, 0, 1}^3
@@ -119,9 +134,8 @@ __global__ __launch_bounds__(256, 2) void k_conv3(Conv3 a) {
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const unsigned blk = xcd_block(blockIdx.x, a.boxes.count);
   if (blk >= (unsigned)a.boxes.count) return;
-  int n, tz, ty, tx;
-  box_at(a.boxes, (int)blk, n, tz, ty, tx);
-  const int z0 = tz * BZ, y0 = ty * RY, x0 = tx * XF;
+  const BoxAt at_box = box_at(a.boxes, (int)blk);
+  const int n = at_box.n, z0 = at_box.z * BZ, y0 = at_box.y * RY, x0 = at_box.x * XF;
   const int n0 = blockIdx.y * NF * 16;
   const Tens &X = a.c.x;
   const uint16_t *xs = X.p + (int64_t)n * X.d * X.h * X.w * X.ld + X.off;
@@ -341,8 +355,9 @@ __global__ __launch_bounds__(256) void k_conv1(ConvP a) {
 // and the next box's loads are on their way while this one is worked on.
 //
 // Measured, 64 x 32 channels over 2^20 positions (116 GFLOP), with the sums of
-// the parts: 184 us (630 TFLOP/s); the general kernel took about 1.9 ms.  Two
-// workgroups per CU with half the registers and no loads ahead: 215 us.
+// the parts, calls back to back: 170 us (680 TFLOP/s); the general kernel took
+// about 1.9 ms.  Two workgroups per CU with half the registers and no loads
+// ahead took 17 % longer.
 //
 // LDS: cells of 64 bytes; their 32-byte halves are swapped by bit 3 of y (x)
 // and of the position's number (g), so that the two groups of 16 lanes that
@@ -377,15 +392,24 @@ __global__ __launch_bounds__(kWgThreads, 3) void k_wgrad3(Wgrad3 a) {
   // position 8 q + j / 4 of a step (and the one four further), channels 4 (j % 4)
   const int k = 8 * q + (j >> 2), yk = k % RY, zk = k / RY;
   // four positions further along y the half may change: two addresses
-  auto x_at = [&](int y, int half) {
-    return ((zk + dz) * XT * YT + y) * 64 + ((half ^ ((y >> 3) & 1)) << 5) + ((j & 3) << 3);
+  auto x_at = [&](int z, int y, int half) {
+    return (z * XT * YT + y) * 64 + ((half ^ ((y >> 3) & 1)) << 5) + ((j & 3) << 3);
   };
   int xa[2][2];
+  // Positions past the grid's end have g = 0, but an infinite x of a cell inside
+  // it times that 0 would be NaN.  So past its last row and plane (zs, ys: those
+  // of the box that are the grid's) a position reads x at its own place, where
+  // it is 0, whatever the tap; and the grid's last column of x does not meet the
+  // column of g after it.  This costs 0 to 2 % of the time; masking x in
+  // registers instead cost 6 %.
+  auto x_rows = [&](int zs, int ys) {
 #pragma unroll
-  for (int h = 0; h < 2; ++h) {
-    xa[h][0] = x_at(yk + dy, h);
-    xa[h][1] = x_at(yk + dy + 4, h);
-  }
+    for (int i = 0; i < 2; ++i) {
+      const bool past = zk >= zs || yk + 4 * i >= ys;
+      xa[0][i] = x_at(zk + (past ? 1 : dz), yk + 4 * i + (past ? 1 : dy), 0);
+      xa[1][i] = xa[0][i] ^ 32;
+    }
+  };
   int ga[2];
 #pragma unroll
   for (int h = 0; h < 2; ++h) ga[h] = k * 64 + ((h ^ (q & 1)) << 5) + ((j & 3) << 3);
@@ -401,11 +425,9 @@ __global__ __launch_bounds__(kWgThreads, 3) void k_wgrad3(Wgrad3 a) {
   constexpr int XC = CELLS * 4, GC = XF * 32 * 4;  // 16-byte pieces of a box
   constexpr int XP = (XC + kWgThreads - 1) / kWgThreads, GP = (GC + kWgThreads - 1) / kWgThreads;
   u4 v[XP + GP];
-  // box b into registers, zero outside the grid ...
-  auto load = [&](int b) {
-    int n, tz, ty, tx;
-    box_at(a.boxes, b, n, tz, ty, tx);
-    const int z0 = tz * RZ, y0 = ty * RY, x0 = tx * XF;
+  // a box into registers, zero outside the grid ...
+  auto load = [&](BoxAt at) {
+    const int n = at.n, z0 = at.z * RZ, y0 = at.y * RY, x0 = at.x * XF;
     const uint16_t *xs = X.p + (int64_t)n * X.d * X.h * X.w * X.ld + X.off + ci0;
     const uint16_t *gs = G.p + (int64_t)n * G.d * G.h * G.w * G.ld + G.off + co0;
     int ft = tid;  // opaque: otherwise every piece's place is kept in registers over the boxes
@@ -428,8 +450,11 @@ __global__ __launch_bounds__(kWgThreads, 3) void k_wgrad3(Wgrad3 a) {
         v[XP + u] = *(const u4 *)(gs + ((gz * G.h + gy) * G.w + gx) * G.ld + 8 * c);
     }
   };
-  // ... from there into LDS, and the loads of the next box on their way
+  // ... from there into LDS, and the loads of the next box on their way;
+  // returns where the box in LDS is
+  BoxAt ahead = box_at(a.boxes, beg);
   auto next = [&](int b) {
+    const BoxAt at = ahead;
     if (b != beg) __syncthreads();
     int ft = tid;
     asm volatile("" : "+v"(ft));
@@ -444,9 +469,11 @@ __global__ __launch_bounds__(kWgThreads, 3) void k_wgrad3(Wgrad3 a) {
       if (i < GC) *(u4 *)(gl + cell * 64 + (((c >> 1) ^ ((kk >> 3) & 1)) << 5) + ((c & 1) << 4)) = v[XP + u];
     }
     __syncthreads();
-    if (b + 1 < end) load(b + 1);
+    ahead = box_after(a.boxes, at);
+    if (b + 1 < end) load(ahead);
+    return at;
   };
-  if (beg < end) load(beg);
+  if (beg < end) load(ahead);
 
   if (wave == 9) {
     // g does not depend on the tap: the tenth wave sums it for the bias, as a product with ones
@@ -477,7 +504,9 @@ __global__ __launch_bounds__(kWgThreads, 3) void k_wgrad3(Wgrad3 a) {
 #pragma unroll
       for (int h = 0; h < 2; ++h) acc[d][m][h] = f4{0.f, 0.f, 0.f, 0.f};
   for (int b = beg; b < end; ++b) {
-    next(b);
+    const BoxAt at = next(b);
+    const int last = G.w - 1 - at.x * XF;
+    x_rows(G.d - at.z * RZ, G.h - at.y * RY);
     // column col of x (from -1) meets columns col - dx of g; one half of x's
     // channels at a time
     bf16x8 gw[3][2], xv[2];
@@ -497,6 +526,7 @@ __global__ __launch_bounds__(kWgThreads, 3) void k_wgrad3(Wgrad3 a) {
         for (int dx = 1; dx >= -1; --dx) {
           const int gc = col - dx;
           if (gc < 0 || gc >= XF) continue;
+          if (dx == -1 && col >= 0 && col == last) continue;  // uniform
 #pragma unroll
           for (int h = 0; h < 2; ++h)
             acc[dx + 1][m][h] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(xv[m], gw[gc % 3][h], acc[dx + 1][m][h], 0, 0, 0);
