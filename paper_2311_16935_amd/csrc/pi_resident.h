@@ -7,6 +7,11 @@
 
 namespace pi {
 
+// Tag of the synchronisation after that of tag t.  Words alternate between two
+// buffers by tag parity, so after the last tag comes 2: 0 is never published,
+// and 1 would use the last one's buffer again while others still read it.
+__host__ __device__ inline uint32_t res_next_tag(uint32_t t) { return t == 0xffffffffu ? 2u : t + 1u; }
+
 // Ring cells of a box: its faces along the march axis, y (3-D) and x, and its
 // corners in the cell-centred scheme.
 __host__ __device__ inline int res_ring(const Inst &in) {

@@ -485,10 +485,7 @@ __device__ __forceinline__ void solve_box(const Inst &in, State *gst, int wg, in
     if (late) sh.abort = 1;
     __syncthreads();
   };
-  auto next_tag = [&] {
-    ++tag;
-    if (tag == 0) ++tag;
-  };
+  auto next_tag = [&] { tag = res_next_tag(tag); };
 
   bool pending = false;  // p, d and alpha of an inner solve wait to be added to P
   T at = T(0);

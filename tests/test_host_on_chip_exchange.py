@@ -1,0 +1,53 @@
+"""Host checks of the on-chip solve's exchange (csrc/pi_resident.h): the
+header's own functions are compiled for the host; no GPU is used."""
+
+import os
+import shutil
+import subprocess
+
+import pytest
+
+ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+
+
+def run_host(tmp_path, name, program):
+    hipcc = shutil.which("hipcc") or "/opt/rocm/bin/hipcc"
+    if not os.path.exists(hipcc):
+        pytest.skip("hipcc not available")
+    src, exe = tmp_path / f"{name}.hip", tmp_path / name
+    src.write_text(program)
+    r = subprocess.run([hipcc, "-std=c++17", "-O2", "--offload-arch=gfx950", "-I",
+                        os.path.join(ROOT, "paper_2311_16935_amd", "csrc"), "-o", str(exe), str(src)],
+                       capture_output=True, text=True, timeout=300)
+    assert r.returncode == 0, r.stderr
+    out = subprocess.run([str(exe)], capture_output=True, text=True, timeout=120, check=True).stdout
+    return [[int(v) for v in ln.split()] for ln in out.splitlines()]
+
+
+TAGS = r"""
+#include <hip/hip_runtime.h>
+#include <cstdio>
+#include "pi_resident.h"
+int main() {
+  for (uint32_t t : {0u, 1u, 2u, 0x7fffffffu, 0xfffffff0u}) {
+    for (int i = 0; i < 40; ++i) {
+      std::printf("%u %u\n", t, pi::res_next_tag(t));
+      t = pi::res_next_tag(t);
+    }
+  }
+}
+"""
+
+
+def test_tags_alternate_between_the_buffers_also_where_they_wrap(tmp_path):
+    """A workgroup overwrites a buffer two synchronisations after it was
+    written: neighbouring tags must differ in parity, and no tag may be 0,
+    which the cleared buffers hold."""
+    steps = run_host(tmp_path, "tags", TAGS)
+    assert any(t == 0xFFFFFFFF for t, _ in steps)
+    for t, n in steps:
+        assert n != 0 and (t ^ n) & 1 == 1, (t, n)
+    # tags near each other are distinct: a buffer never holds the tag that is awaited next
+    for i in range(len(steps) - 3):
+        if i % 40 < 37:
+            assert len({s[1] for s in steps[i:i + 3]}) == 3
