@@ -243,7 +243,7 @@ struct Inst {
   const uint8_t *res_has; // ... bit j: neighbour j holds data
   int64_t res_words;      // exchange words of one tag parity: [res_nwg + kResGroups][8] of partial sums,
                           // then [res_nwg][ring cells] of face cells (two words each in FP64)
-  uint64_t *res_x;        // both parities
+  uint64_t *res_x;        // both parities, and a word for a workgroup that gave up waiting (res_late_word)
   // per-solve user buffers
   const void *g[3];
   void *Pout;

@@ -24,6 +24,7 @@
 #include "pi_common.h"
 #include "pi_device.h"
 #include "pi_kernels.h"
+#include "pi_resident.h"
 
 namespace pi {
 
@@ -602,10 +603,11 @@ __global__ __launch_bounds__(kBlock) void k_init(const BlockEnt *tab, const Inst
     }
     P[c] = x;
   }
-  // exchange words of the on-chip solve: tag 0, which it never publishes
+  // exchange words of the on-chip solve: tag 0, which it never publishes, and
+  // no workgroup late
   if (in.res_nwg > 1) {
-    const int64_t per = (2 * in.res_words + in.nblocks - 1) / in.nblocks;
-    const int64_t wb = min(2 * in.res_words, e.lb * per), we = min(2 * in.res_words, wb + per);
+    const int64_t words = res_late_word(in) + 1, per = (words + in.nblocks - 1) / in.nblocks;
+    const int64_t wb = min(words, e.lb * per), we = min(words, wb + per);
     for (int64_t w = wb + threadIdx.x; w < we; w += kBlock) in.res_x[w] = 0;
   }
   if (bad) atomicOr(&st->nonfinite, 1);
@@ -1966,6 +1968,7 @@ __global__ __launch_bounds__(kBlock) void k_finalize(const Inst *__restrict__ in
       if (skip_outer(st)) return;
       break;
     case K_GAUGE_SUM:
+      if (in.res_nwg > 1 && threadIdx.x == 0) (void)res_late(*st, in.res_x[res_late_word(in)]);
       if (in.ncomp > 1) return;
       break;
     case K_CG_STEP:

@@ -757,7 +757,7 @@ extern "C" pi_status pi_plan(int ndim, const int64_t dims[3], const double spaci
     PI_TRY(plan_alloc(p, (void **)&p->d_tab_res, tab.size() * sizeof(BlockEnt)));
     // words of two tag parities: 8 for a workgroup's or group's sums, then the face cells
     in.res_words = 8 * (int64_t)(in.res_nwg + kResGroups) + (int64_t)in.res_nwg * res_ring(in) * (T / 4);
-    PI_TRY(plan_alloc(p, (void **)&p->res_x, 2 * in.res_words * sizeof(uint64_t)));
+    PI_TRY(plan_alloc(p, (void **)&p->res_x, (res_late_word(in) + 1) * sizeof(uint64_t)));
     PI_TRY(hipMemcpy(p->d_tab_res, tab.data(), tab.size() * sizeof(BlockEnt), hipMemcpyHostToDevice));
     in.res_x = p->res_x;
   }

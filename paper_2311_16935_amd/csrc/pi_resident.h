@@ -12,6 +12,19 @@ namespace pi {
 // and 1 would use the last one's buffer again while others still read it.
 __host__ __device__ inline uint32_t res_next_tag(uint32_t t) { return t == 0xffffffffu ? 2u : t + 1u; }
 
+// A workgroup whose wait has lasted too long says so in the word after the
+// exchange words of both parities (cleared with them when a solve starts).
+// The next launch of the solve, and the sums of the gauge after the last, turn
+// it into the solve's status: the workgroup that holds the state may have
+// missed nothing itself and store any other.
+inline __host__ __device__ int64_t res_late_word(const Inst &in) { return 2 * in.res_words; }
+__host__ __device__ inline bool res_late(State &st, uint64_t word) {
+  if (word == 0) return false;
+  st.done = 1;
+  st.status = 6;  // PI_ERR_DEVICE
+  return true;
+}
+
 // Ring cells of a box: its faces along the march axis, y (3-D) and x, and its
 // corners in the cell-centred scheme.
 __host__ __device__ inline int res_ring(const Inst &in) {

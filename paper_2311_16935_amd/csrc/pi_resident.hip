@@ -686,11 +686,9 @@ __device__ __forceinline__ void solve_box(const Inst &in, State *gst, int wg, in
       if ((have >> j) & 1u) gP[c0 + j * sm] = Pr[j];
   }
   __syncthreads();
+  if (aborted && t == 0) put(words + res_late_word(in), 1);
   if (wg == 0 && t == 0) {
-    if (aborted) {
-      sh.st.done = 1;
-      sh.st.status = 6;  // PI_ERR_DEVICE
-    }
+    (void)res_late(sh.st, aborted);
     sh.st.tag = tag;
     *gst = sh.st;
   }
@@ -708,6 +706,13 @@ __global__ __launch_bounds__(kRB) void k_resident(const BlockEnt *tab, const Ins
   const Inst &in = insts[e.inst];
   State *st = sts + e.inst;
   if (st->done) return;  // the same for every workgroup of the grid: only its last launch sets it
+  if (in.res_nwg > 1) {
+    const u64 late = get((PI_G u64 *)in.res_x + res_late_word(in));
+    if (late != 0) {  // of an earlier launch
+      if (e.lb == 0 && threadIdx.x == 0) (void)res_late(*st, late);
+      return;
+    }
+  }
   const bool opl = in.inner_op != 0;
 #define PI_BOX(ND, N, HJ)                                                        \
   do {                                                                           \

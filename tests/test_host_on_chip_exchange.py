@@ -51,3 +51,39 @@ def test_tags_alternate_between_the_buffers_also_where_they_wrap(tmp_path):
     for i in range(len(steps) - 3):
         if i % 40 < 37:
             assert len({s[1] for s in steps[i:i + 3]}) == 3
+
+
+LATE = r"""
+#include <hip/hip_runtime.h>
+#include <cstdio>
+#include <cstring>
+#include "pi_resident.h"
+int main() {
+  pi::Inst in;
+  std::memset(&in, 0, sizeof in);
+  in.res_words = 1234;
+  for (int done = 0; done < 2; ++done)
+    for (int status : {0, 3, 4, 5})
+      for (unsigned long long word : {0ull, 1ull}) {
+        pi::State st;
+        std::memset(&st, 0, sizeof st);
+        st.done = done;
+        st.status = status;
+        st.outer = 7;
+        const int late = pi::res_late(st, word);
+        std::printf("%d %d %d %d %d %d %lld %lld\n", done, status, (int)word, late, st.done, st.status,
+                    (long long)st.outer, (long long)pi::res_late_word(in));
+      }
+}
+"""
+
+
+def test_a_workgroup_that_gave_up_waiting_decides_the_status(tmp_path):
+    """Whatever the workgroup that holds the state has stored, a late
+    workgroup's word ends the solve with PI_ERR_DEVICE; without one nothing
+    changes.  The word lies behind the exchange words of both parities."""
+    rows = run_host(tmp_path, "late", LATE)
+    assert len(rows) == 16
+    for done, status, word, late, done1, status1, outer, at in rows:
+        assert late == word and outer == 7 and at == 2 * 1234
+        assert (done1, status1) == ((1, 6) if word else (done, status))
