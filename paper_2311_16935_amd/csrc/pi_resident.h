@@ -2,6 +2,7 @@
 #pragma once
 
 #include <algorithm>
+#include <vector>
 
 #include "pi_common.h"
 
@@ -107,6 +108,25 @@ inline void set_resident(Inst &in, bool fp64, int cus) {
       }
     }
   }
+}
+
+// Grids of a batch that go onto the chip next: from `todo` (in its order) into
+// `on` whatever fits beside those there; wgs(i): workgroups of grid i.  False
+// where nothing is on the chip then though grids wait.
+template <class F>
+inline bool res_admit(std::vector<int64_t> &todo, std::vector<int64_t> &on, int max_wg, F &&wgs) {
+  int used = 0;
+  for (int64_t i : on) used += wgs(i);
+  for (auto it = todo.begin(); it != todo.end();) {
+    if (used + wgs(*it) > max_wg) {
+      ++it;
+      continue;
+    }
+    used += wgs(*it);
+    on.push_back(*it);
+    it = todo.erase(it);
+  }
+  return !on.empty();
 }
 
 }  // namespace pi

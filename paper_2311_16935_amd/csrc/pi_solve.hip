@@ -492,17 +492,8 @@ struct OnChip {
     std::vector<BlockEnt> t;
     std::vector<int64_t> ends;
     while (!todo.empty() || !on.empty()) {
-      int used = 0;
-      for (int64_t i : on) used += b.host[i].res_nwg;
-      for (auto it = todo.begin(); it != todo.end();) {
-        if (used + b.host[*it].res_nwg > max_wg) {
-          ++it;
-          continue;
-        }
-        used += b.host[*it].res_nwg;
-        on.push_back(*it);
-        it = todo.erase(it);
-      }
+      // a device with fewer CUs than the plan's: nothing would ever fit
+      if (!res_admit(todo, on, max_wg, [&](int64_t i) { return b.host[i].res_nwg; })) return PI_ERR_DEVICE;
       t.clear();
       size_t lds = 0;
       bool coop = false;

@@ -87,3 +87,36 @@ def test_a_workgroup_that_gave_up_waiting_decides_the_status(tmp_path):
     for done, status, word, late, done1, status1, outer, at in rows:
         assert late == word and outer == 7 and at == 2 * 1234
         assert (done1, status1) == ((1, 6) if word else (done, status))
+
+
+ADMIT = r"""
+#include <hip/hip_runtime.h>
+#include <cstdio>
+#include "pi_resident.h"
+int main() {
+  const int wg[] = {200, 100, 60, 56, 1, 256};
+  for (int max_wg : {256, 100, 1, 0})
+    for (int first = -1; first < 6; ++first) {
+      std::vector<int64_t> todo, on;
+      int used = 0;
+      for (int i = 0; i < 6; ++i) (i == first ? on : todo).push_back(i);
+      const bool ok = pi::res_admit(todo, on, max_wg, [&](int64_t i) { return wg[i]; });
+      for (int64_t i : on) used += wg[i];
+      std::printf("%d %d %d %d %d %d\n", max_wg, first, (int)ok, used, (int)on.size(), (int)todo.size());
+    }
+}
+"""
+
+
+def test_a_batch_whose_grids_do_not_fit_the_device_ends(tmp_path):
+    """Grids go onto the chip in order as far as they fit; where none fits and
+    none runs, that is said, so that the loop over the rounds ends."""
+    rows = {(m, f): r for m, f, *r in run_host(tmp_path, "admit", ADMIT)}
+    assert rows[(256, -1)] == [1, 256, 2, 4]  # 200 and 56: 100 and 60 would not fit beside the first
+    assert rows[(256, 5)] == [1, 256, 1, 5]   # one that fills the device
+    assert rows[(256, 2)] == [1, 217, 4, 2]   # beside a running one of 60: 100, 56 and 1
+    assert rows[(100, -1)] == [1, 100, 1, 5]
+    assert rows[(1, -1)] == [1, 1, 1, 5]
+    assert rows[(0, -1)] == [0, 0, 0, 6]
+    for (m, f), (ok, used, n_on, n_todo) in rows.items():
+        assert n_on + n_todo == 6 and ok == (n_on > 0)
