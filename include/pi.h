@@ -103,7 +103,8 @@ typedef struct pi_info {
   int32_t status;            /* pi_status of this instance                      */
   int32_t components;        /* connected groups of data cells                  */
   int32_t worklist_rebuilds; /* batched calls: times finished instances left the
-                                work list while others ran (0 for pi_solve)    */
+                                work list while others ran or waited (0 for
+                                pi_solve)                                      */
   int32_t reserved;
 } pi_info;
 
@@ -229,8 +230,10 @@ pi_status pi_last_info(pi_plan_t plan, pi_info *info);
  * rebuilds the work list without them and captures the graph again
  * (pi_info.worklist_rebuilds counts this).  Instances that pi_solve would
  * solve on the chip (see pi_set_tile) are solved there first, as many side by
- * side as the device holds; a finished one gives up its place at once, and
- * pi_info.worklist_rebuilds counts these too.  An instance returns what its
+ * side as the device holds; waiting ones take the places of finished ones
+ * after each launch (of at most 4096 passes), and pi_info.worklist_rebuilds
+ * counts, for each launch, the different numbers of passes after which some
+ * ended, without the call's last.  An instance returns what its
  * own pi_solve returns, bit for bit, when both run on the chip.
  *   count         number of instances (>= 1); plans[i] must be distinct and
  *                 share the precision flag.

@@ -478,7 +478,9 @@ pi_status batch_setup(int64_t count, const pi_plan_t *plans, const void *const *
 // states; the launcher's instance records and states are set up.
 struct OnChip {
   std::vector<int64_t> todo;
-  int left_early = 0;  // times a grid finished while another was running
+  // times grids finished while others of the batch ran or waited: in each
+  // launch once for every number of synchronisations after which some ended
+  int left_early = 0;
 
   explicit OnChip(const BatchSetup &b) {
     for (size_t i = 0; i < b.host.size(); ++i)
@@ -490,7 +492,7 @@ struct OnChip {
   pi_status run(const BatchSetup &b, const Launcher &L, BlockEnt *tab, int max_wg, State *hst, hipStream_t stream) {
     std::vector<int64_t> on;
     std::vector<BlockEnt> t;
-    std::vector<int64_t> ends;
+    std::vector<int64_t> tag(b.host.size(), 0), ends;  // synchronisations so far; of one launch's finished grids
     while (!todo.empty() || !on.empty()) {
       // a device with fewer CUs than the plan's: nothing would ever fit
       if (!res_admit(todo, on, max_wg, [&](int64_t i) { return b.host[i].res_nwg; })) return PI_ERR_DEVICE;
@@ -509,15 +511,18 @@ struct OnChip {
           hipStreamSynchronize(stream) != hipSuccess)
         return PI_ERR_DEVICE;
       std::vector<int64_t> still;
+      ends.clear();
       for (int64_t i : on) {
-        if (hst[i].done) ends.push_back(hst[i].tag);
+        if (hst[i].done) ends.push_back(hst[i].tag - tag[i]);
         else still.push_back(i);
+        tag[i] = hst[i].tag;
       }
       on.swap(still);
+      std::sort(ends.begin(), ends.end());
+      left_early += (int)(std::unique(ends.begin(), ends.end()) - ends.begin());
     }
-    std::sort(ends.begin(), ends.end());
-    left_early = (int)(std::unique(ends.begin(), ends.end()) - ends.begin());
-    if (left_early > 0 && ends.size() > 0 && (size_t)b.on_chip == b.host.size()) --left_early;
+    // the last to finish left nobody behind
+    if (left_early > 0 && (size_t)b.on_chip == b.host.size()) --left_early;
     return PI_OK;
   }
 };
