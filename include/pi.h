@@ -233,8 +233,10 @@ pi_status pi_last_info(pi_plan_t plan, pi_info *info);
  * side as the device holds; waiting ones take the places of finished ones
  * after each launch (of at most 4096 passes), and pi_info.worklist_rebuilds
  * counts, for each launch, the different numbers of passes after which some
- * ended, without the call's last.  An instance returns what its
- * own pi_solve returns, bit for bit, when both run on the chip.
+ * ended, without the call's last.  Where a batch of many mid-size 2-D grids
+ * (some 100^2 to 300^2 cells) would take longer on the chip, all of it streams.
+ * An instance returns what its own pi_solve returns, bit for bit, when both run
+ * on the chip.
  *   count         number of instances (>= 1); plans[i] must be distinct and
  *                 share the precision flag.
  *   gx, gy, gz, P host arrays of `count` device pointers, as for pi_solve

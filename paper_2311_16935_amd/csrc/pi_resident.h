@@ -110,6 +110,20 @@ inline void set_resident(Inst &in, bool fp64, int cus) {
   }
 }
 
+// ---------------------------------------------------------------------------
+// batches: grids side by side on the chip, or streamed in one set of launches
+// ---------------------------------------------------------------------------
+// Grids that are solved on the chip, in the order they get there: the longest
+// sides first (they take the most outer steps).
+inline std::vector<int64_t> res_queue(const std::vector<Inst> &insts) {
+  std::vector<int64_t> q;
+  for (size_t i = 0; i < insts.size(); ++i)
+    if (insts[i].res_nwg > 0) q.push_back((int64_t)i);
+  auto side = [&](int64_t i) { return std::max({insts[i].nx, insts[i].ny, insts[i].nz}); };
+  std::stable_sort(q.begin(), q.end(), [&](int64_t x, int64_t y) { return side(x) > side(y); });
+  return q;
+}
+
 // Grids of a batch that go onto the chip next: from `todo` (in its order) into
 // `on` whatever fits beside those there; wgs(i): workgroups of grid i.  False
 // where nothing is on the chip then though grids wait.
@@ -127,6 +141,78 @@ inline bool res_admit(std::vector<int64_t> &todo, std::vector<int64_t> &on, int 
     it = todo.erase(it);
   }
   return !on.empty();
+}
+
+// Passes a grid is expected to take (their number enters both sides alike):
+// about 16 outer steps per cell of the longest side, the fixed-point variant
+// about 8 passes.
+inline double batch_passes(const Inst &in) {
+  const double side = std::max({in.nx, in.ny, in.nz}), per = in.inner_iters + 1.0;
+  return std::min((double)in.max_iter * per, in.inner_op ? 8.0 * side : 16.0 * side * per);
+}
+
+// Microseconds of a pass on the chip as measured in batches: res_cost, which
+// ranks one grid's boxes, is 20 % too high where two hops are taken, and too
+// low for FP64, the cell-centred scheme and 3-D.
+inline double batch_chip_us(const Inst &in, bool fp64) {
+  return res_cost(in, in.res_r, res_ring(in), in.res_nwg) * (in.res_nwg > 64 ? 0.8 : 1.0) * (fp64 ? 1.2 : 1.0) *
+         (in.cc ? 1.1 : in.ndim == 3 ? 1.1 : 1.0);
+}
+
+// Microseconds a grid adds to a streaming pass over many: per block, by cells
+// per lane, for segments of four planes.  Each pass takes kStreamUs besides for
+// every launch shape among the grids.
+constexpr double kStreamUs = 11.0;
+inline double batch_stream_us(const Inst &in, bool fp64) {
+  const int v = in.vw == 4 ? 2 : in.vw == 2 ? 1 : 0;
+  constexpr double face[3] = {0.0065, 0.010, 0.020}, face64[3] = {0.009, 0.018, 0.045}, cell[3] = {0.0103, 0.018, 0.036};
+  const double t = in.cc ? cell[v] * (fp64 ? 2.0 : 1.0) : fp64 ? face64[v] : face[v];
+  return t * in.nblocks * in.mseg / 4.0;
+}
+
+// Where a batch had better stream than solve on the chip what fits there: every
+// res_nwg is set to 0.  A grid's boxes are chosen for its own latency, with as
+// few cells per lane as there are workgroups, so that grids of some 100^2 to
+// 300^2 cells take turns on the device at one cell per lane, and many of them
+// stream faster (24 outer steps, on the chip and streamed: 400 of 101^2 10.7
+// and 7.0 ms, 300 of 300 x 200 78 and 53 ms, 300 of 1000 x 30 91 and 31 ms).
+// Few of them, smaller ones (one workgroup each) and larger ones (more cells
+// per lane) are faster on the chip (24 of 101^2 1.0 and 1.8 ms, 60 of 64^3 14
+// and 49 ms), and so are batches of many launch shapes (200 with sides of 100 to
+// 500: 43 and 54 ms).  Estimated, by the figures above, for the rounds on the
+// chip and for passes over the same grids streamed (apart from those that
+// stream anyway).  The estimates are rough (up to 40 % off); in each of some 60
+// batches timed both ways they picked the faster one, or one 2 % slower at most.
+inline void batch_routes(std::vector<Inst> &insts, bool fp64, int max_wg, int syncs) {
+  std::vector<int64_t> todo = res_queue(insts), on;
+  std::vector<double> left(insts.size());
+  double longest = 0.0, stream = 0.0, chip = 0.0;
+  bool shape[kShapes] = {};
+  for (int64_t i : todo) {
+    const Inst &in = insts[i];
+    shape[shape_of(in.ndim, in.vw, in.gen, in.cc)] = true;
+    left[i] = batch_passes(in);
+    longest = std::max(longest, left[i]);
+    stream += left[i] * batch_stream_us(in, fp64);
+  }
+  stream += kStreamUs * longest * (double)std::count(shape, shape + kShapes, true);
+  while (!todo.empty() || !on.empty()) {
+    if (!res_admit(todo, on, max_wg, [&](int64_t i) { return insts[i].res_nwg; })) return;
+    double us = 0.0;
+    std::vector<int64_t> still;
+    for (int64_t i : on) {
+      const double run = std::min(left[i], (double)syncs);
+      us = std::max(us, run * batch_chip_us(insts[i], fp64));
+      left[i] -= run;
+      if (left[i] > 0.0) still.push_back(i);
+    }
+    on.swap(still);
+    chip += us + 40.0;  // a launch, and the host between two
+    if (chip > stream) {
+      for (Inst &in : insts) in.res_nwg = 0;
+      return;
+    }
+  }
 }
 
 }  // namespace pi

@@ -425,6 +425,15 @@ hipError_t upload_live_tables(BatchSetup &b, const WorkList &wl, Launcher &L, hi
   return hipStreamSynchronize(stream);
 }
 
+// CUs of the current device, at most kResMaxWg: workgroups of a launch of the on-chip solve.
+int resident_workgroups() {
+  int dev = 0, cus = 0;
+  if (hipGetDevice(&dev) != hipSuccess ||
+      hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess)
+    return 0;
+  return std::min(cus, kResMaxWg);
+}
+
 pi_status batch_setup(int64_t count, const pi_plan_t *plans, const void *const *gx, const void *const *gy,
                       const void *const *gz, void *const *P, const double *tol, int64_t max_iter, uint32_t flags,
                       BatchSetup &b) {
@@ -440,8 +449,11 @@ pi_status batch_setup(int64_t count, const pi_plan_t *plans, const void *const *
     b.host[i] = p->inst;
     if (!set_user(b.host[i], p, gx[i], gy[i], gz ? gz[i] : nullptr, P[i], tol[i], max_iter, flags))
       return PI_ERR_INVALID_ARG;
-    if (p->inst.res_nwg > 0) ++b.on_chip;
-    else b.inner = std::max(b.inner, p->inner_iters);
+  }
+  batch_routes(b.host, b.fp64, resident_workgroups(), kResSyncs);
+  for (const Inst &h : b.host) {
+    if (h.res_nwg > 0) ++b.on_chip;
+    else b.inner = std::max(b.inner, h.inner_iters);
   }
   std::vector<Inst *> by[kShapes];
   for (int64_t i = 0; i < count; ++i) {
@@ -472,9 +484,8 @@ pi_status batch_setup(int64_t count, const pi_plan_t *plans, const void *const *
 }
 
 // Grids that are solved on the chip, several at a time as far as their
-// workgroups fit the device together: the longest sides first (they take the
-// most outer steps), and after each launch waiting grids take the places of
-// finished ones.  `tab` (device) holds kResMaxWg entries, `hst` (host) count
+// workgroups fit the device together, and after each launch waiting grids take
+// the places of finished ones.  `tab` (device) holds kResMaxWg entries, `hst` (host) count
 // states; the launcher's instance records and states are set up.
 struct OnChip {
   std::vector<int64_t> todo;
@@ -482,12 +493,7 @@ struct OnChip {
   // launch once for every number of synchronisations after which some ended
   int left_early = 0;
 
-  explicit OnChip(const BatchSetup &b) {
-    for (size_t i = 0; i < b.host.size(); ++i)
-      if (b.host[i].res_nwg > 0) todo.push_back((int64_t)i);
-    auto side = [&](int64_t i) { return std::max({b.host[i].nx, b.host[i].ny, b.host[i].nz}); };
-    std::stable_sort(todo.begin(), todo.end(), [&](int64_t x, int64_t y) { return side(x) > side(y); });
-  }
+  explicit OnChip(const BatchSetup &b) : todo(res_queue(b.host)) {}
 
   pi_status run(const BatchSetup &b, const Launcher &L, BlockEnt *tab, int max_wg, State *hst, hipStream_t stream) {
     std::vector<int64_t> on;
@@ -526,15 +532,6 @@ struct OnChip {
     return PI_OK;
   }
 };
-
-// CUs of the current device, at most kResMaxWg: workgroups of a launch of the on-chip solve.
-int resident_workgroups() {
-  int dev = 0, cus = 0;
-  if (hipGetDevice(&dev) != hipSuccess ||
-      hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess)
-    return 0;
-  return std::min(cus, kResMaxWg);
-}
 
 pi_status batch_report(int64_t count, const pi_plan_t *plans, const State *hst, pi_info *infos,
                        std::chrono::steady_clock::time_point t0, int rebuilds) {
