@@ -627,6 +627,7 @@ bool wgrad_fast(const WgP &a, int nsplit, hipStream_t s) {
   const bool wide = padded(16) <= padded(8);
   const int ry = wide ? 16 : 8;
   w.boxes = boxes_of(a.x.n, a.md, a.mh, a.mw, 32 / ry, ry, 8);
+  if (!wgrad_boxes_pay(w.boxes.count, a.P, nsplit, a.cin, a.cout)) return false;
   const dim3 grid((unsigned)nsplit, (unsigned)((a.cin + 31) / 32 * w.cts));
   if (wide && xvec) k_wgrad3<16, true><<<grid, kWgThreads, 0, s>>>(w);
   else if (wide) k_wgrad3<16, false><<<grid, kWgThreads, 0, s>>>(w);
