@@ -343,8 +343,10 @@ int32_t pi_get_cg_recompute(pi_plan_t plan);
  * 4 * reps launches and keeps the fastest of those; then it chooses between
  * plain and non-temporal streams in the outer kernel (4 * reps launches each).  Results are
  * cached per (ndim, dims, precision, inner solver) for the life of the process,
- * so later plans of the same shape take the cached tile without timing.  The
- * chosen segment length is returned in *mseg (may be NULL).  Overwrites the
+ * so later plans of the same shape take the cached tile without timing.  On a
+ * plan that is solved on the chip (see pi_set_tile) the tile is that of pi_apply
+ * alone, which is timed in place of the solve's kernels; the solve stays on the
+ * chip.  The chosen segment length is returned in *mseg (may be NULL).  Overwrites the
  * plan's workspace; synchronous.  The paper has no counterpart (its kernels
  * use one fixed launch shape); the knob changes speed, never results.
  */

@@ -76,6 +76,10 @@ void set_walk(Inst &in, int ndim, const int64_t dims[3], int mseg_override, int 
 // Single-instance table and partial slots of a plan.
 hipError_t plan_tables(pi_plan_s *p);
 
+// pi_set_tile; on_chip: a plan that fits the chip is solved there all the same
+// (the tile is that of its operator applies).
+pi_status plan_set_tile(pi_plan_s *p, int32_t mseg, int32_t lane_cells, bool on_chip);
+
 // Block table of a set of instances, XCD-aware.  With assign_parts the
 // instances' partial-sum slots are numbered from part_base0 on (else their
 // part_base is kept: a table rebuilt for a subset of a batch).

@@ -810,6 +810,11 @@ extern "C" void pi_plan_destroy(pi_plan_t p) {
 extern "C" size_t pi_workspace_bytes(pi_plan_t p) { return p ? p->bytes : 0; }
 
 extern "C" pi_status pi_set_tile(pi_plan_t p, int32_t mseg, int32_t lane_cells) {
+  // a tile asked for is a tile used: the solve streams
+  return plan_set_tile(p, mseg, lane_cells, mseg == 0 && lane_cells == 0);
+}
+
+pi_status pi::plan_set_tile(pi_plan_s *p, int32_t mseg, int32_t lane_cells, bool on_chip) {
   if (!p || mseg < 0 || (lane_cells != 0 && lane_cells != 1 && lane_cells != 2 && lane_cells != 4))
     return PI_ERR_INVALID_ARG;
   if (lane_cells == 4 && p->dims[0] % 4 != 0) return PI_ERR_INVALID_ARG;
@@ -821,7 +826,7 @@ extern "C" pi_status pi_set_tile(pi_plan_t p, int32_t mseg, int32_t lane_cells) 
   p->graph = nullptr;
   p->graph_key = -1;
   set_walk(p->inst, p->ndim, p->dims, mseg, lane_cells);
-  p->inst.res_nwg = mseg == 0 && lane_cells == 0 ? p->res_nwg : 0;  // a tile asked for is a tile used
+  p->inst.res_nwg = on_chip ? p->res_nwg : 0;
   if (plan_tables(p) != hipSuccess) return PI_ERR_OOM;
   if (hipMemcpy(p->d_inst, &p->inst, sizeof(Inst), hipMemcpyHostToDevice) != hipSuccess) return PI_ERR_DEVICE;
   return PI_OK;

@@ -956,14 +956,16 @@ extern "C" pi_status pi_time_kernel(pi_plan_t p, int kernel, int32_t reps, doubl
                        [&] { return L.go(k, stream, timed_pass(L, i++), nullptr, nullptr, false); });
 }
 
-// tile cache of pi_autotune: (ndim, nx, ny, nz, fp64, bicgstab) -> (mseg, lane cells, non-temporal outer)
+// tile cache of pi_autotune: (ndim, nx, ny, nz, fp64, solver: BiCGStab 1, cell-centred 2, on the chip 4) ->
+// (mseg, lane cells, non-temporal outer)
 static std::mutex g_tune_mu;
 static std::map<std::array<int64_t, 6>, std::array<int32_t, 3>> g_tune;
 
 extern "C" pi_status pi_autotune(pi_plan_t p, int32_t reps, int32_t *mseg_out, void *stream) {
   if (!p || reps < 1) return PI_ERR_INVALID_ARG;
+  const bool chip = p->res_nwg > 0;  // solved on the chip: the tile is that of the operator applies
   const std::array<int64_t, 6> key = {p->ndim, p->dims[0], p->dims[1], p->dims[2], p->fp64,
-                                      (p->bicgstab ? 1 : 0) | (p->cc ? 2 : 0)};
+                                      (p->bicgstab ? 1 : 0) | (p->cc ? 2 : 0) | (chip ? 4 : 0)};
   std::array<int32_t, 3> best = {-1, 0, 0};
   {
     std::lock_guard<std::mutex> g(g_tune_mu);
@@ -971,11 +973,6 @@ extern "C" pi_status pi_autotune(pi_plan_t p, int32_t reps, int32_t *mseg_out, v
     if (it != g_tune.end()) best = it->second;
   }
   pi_status rc;
-  if (p->res_nwg > 0) {  // solved on the chip: the solve has no tile to time
-    rc = pi_set_tile(p, 0, 0);
-    if (rc == PI_OK && mseg_out) *mseg_out = p->inst.mseg;
-    return rc;
-  }
   if (best[0] < 0) {
     std::vector<std::array<int32_t, 2>> cand;
     p->inst.nt_outer = 0;
@@ -989,10 +986,15 @@ extern "C" pi_status pi_autotune(pi_plan_t p, int32_t reps, int32_t *mseg_out, v
       for (int32_t m = 2; m <= 256; m *= 2)
         if (m < p->inst.nm && m != p->inst.mseg) cand.push_back({m, vw});
     }
-    // time of one outer step at a candidate tile
+    // time of one outer step (on the chip: of an operator apply) at a candidate tile
     auto step_ms = [&](const std::array<int32_t, 2> &c, int32_t r, double *ms) -> pi_status {
       pi_status e;
-      if ((e = pi_set_tile(p, c[0], c[1])) != PI_OK) return e;
+      if ((e = plan_set_tile(p, c[0], c[1], chip)) != PI_OK) return e;
+      if (chip) {
+        const Launcher L = single_launcher(p);
+        return time_launches((hipStream_t)stream, r, ms,
+                             [&] { return L.go(K_APPLY, (hipStream_t)stream, PI_OP_M, p->p[0], p->q); });
+      }
       double t_outer = 0.0, t_first = 0.0, t_inner = 0.0;
       if ((e = pi_time_kernel(p, PI_K_OUTER, r, &t_outer, stream)) != PI_OK) return e;
       if (!p->bicgstab && p->inner_iters > 0) {
@@ -1023,9 +1025,9 @@ extern "C" pi_status pi_autotune(pi_plan_t p, int32_t reps, int32_t *mseg_out, v
       }
     }
     // at the chosen tile: the outer kernel's streams plain or non-temporal
-    if ((rc = pi_set_tile(p, best[0], best[1])) != PI_OK) return rc;
+    if ((rc = plan_set_tile(p, best[0], best[1], chip)) != PI_OK) return rc;
     double t_nt[2] = {0.0, 0.0};
-    for (int nt = 0; nt < 2; ++nt) {
+    for (int nt = 0; nt < 2 && !chip; ++nt) {
       p->inst.nt_outer = nt;
       if ((rc = pi_time_kernel(p, PI_K_OUTER, 4 * reps, &t_nt[nt], stream)) != PI_OK) return rc;
     }
@@ -1034,7 +1036,7 @@ extern "C" pi_status pi_autotune(pi_plan_t p, int32_t reps, int32_t *mseg_out, v
     g_tune[key] = best;
   }
   p->inst.nt_outer = best[2];
-  rc = pi_set_tile(p, best[0], best[1]);
+  rc = plan_set_tile(p, best[0], best[1], chip);
   if (rc == PI_OK && mseg_out) *mseg_out = p->inst.mseg;
   return rc;
 }
