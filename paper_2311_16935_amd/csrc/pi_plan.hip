@@ -644,12 +644,12 @@ extern "C" pi_status pi_plan(int ndim, const int64_t dims[3], const double spaci
   in.inv_nvalid = 1.0 / (double)nvalid;
 
   // counter codes from the mask
+  PI_TRY(plan_alloc(p, (void **)&p->code, N * sizeof(uint32_t)));
   uint8_t *d_mask = nullptr;
   if (hipMalloc((void **)&d_mask, N) != hipSuccess) {
     pi_plan_destroy(p);
     return PI_ERR_OOM;
   }
-  PI_TRY(plan_alloc(p, (void **)&p->code, N * sizeof(uint32_t)));
   if (hipMemcpy(d_mask, m, N, hipMemcpyHostToDevice) != hipSuccess ||
       (p->cc ? launch_codes_cc((int)p->dims[0], (int)p->dims[1], d_mask, p->code)
              : launch_codes(ndim, (int)p->dims[0], (int)p->dims[1], (int)p->dims[2], d_mask, p->code, nullptr)) !=
