@@ -678,9 +678,10 @@ extern "C" pi_status pi_plan(int ndim, const int64_t dims[3], const double spaci
   // callers get the iterates they always had.  FP32 vectors round such
   // differences away.
   if (!p->fp64 || p->fixed_point || (!mask && !p->cc)) {
-    if (p->cc && ring_codes(p, in) != PI_OK) {
+    const pi_status rc = p->cc ? ring_codes(p, in) : PI_OK;
+    if (rc != PI_OK) {
       pi_plan_destroy(p);
-      return PI_ERR_OOM;
+      return rc;
     }
     set_resident(in, p->fp64, coop ? cus : 1);
   }

@@ -135,3 +135,8 @@ def test_a_plan_that_fails_leaves_nothing_and_says_why(tmp_path):
         assert not made, what
         assert rc in ((pi.PI_ERR_OOM,) if fm >= 0 else (pi.PI_ERR_DEVICE, pi.PI_ERR_OOM)), what
     assert fails > 100
+    # cell-centred plans (cases 1 and 2): the mask's copy, then the ring codes' copies
+    # (the codes to the host; numbers, weights and neighbour bits back)
+    for case in (1, 2):
+        status = {fc: rc for c, _, fc, rc, *_ in rows if c == case and fc >= 0}
+        assert [status[k] for k in range(5)] == [pi.PI_ERR_DEVICE] * 5, status
