@@ -46,7 +46,9 @@ typedef enum pi_status {
   PI_ERR_NONFINITE = 3,     /* a data cell holds a NaN or infinite gradient    */
   PI_ERR_NOT_CONVERGED = 4, /* max_iter outer steps without reaching tol       */
   PI_ERR_DIVERGED = 5,      /* the residual became non-finite                  */
-  PI_ERR_DEVICE = 6,        /* a HIP runtime call failed                       */
+  PI_ERR_DEVICE = 6,        /* a HIP runtime call failed, or a solve on the chip
+                               (see pi_set_tile) whose workgroups wait for each
+                               other waited 20 s for one: P is not valid then  */
   PI_ERR_TOO_LARGE = 7      /* beyond pi_solve_batched_noalloc's fixed scratch */
 } pi_status;
 
@@ -157,11 +159,14 @@ pi_status pi_set_inner_iters(pi_plan_t plan, int32_t iters);
  * Solves whose vectors fit the registers of the device run on the chip, in
  * one kernel without a tile (CG: FP32 up to 4 M cells in 2-D and 2 M in 3-D,
  * with PI_CELL_CENTERED where the mask has at most some 600 different
- * neighbourhoods; FP64 up to half of that, with PI_FIXED_POINT_CG or without
- * a mask and PI_CELL_CENTERED), while mseg and lane_cells are both 0, the
- * default.  A tile asked for here is used: the solve then streams its vectors
- * through memory.  Either way the arithmetic per cell is the same; the FP64
- * sums are added in another order.
+ * neighbourhoods; FP64 up to half of that with PI_FIXED_POINT_CG, and in the
+ * face-crossing scheme on plans made without a mask), while mseg and lane_cells
+ * are both 0, the default.  A tile asked for here is used: the solve then
+ * streams its vectors through memory.  Either way the arithmetic per cell is the
+ * same; the FP64 sums are added in another order.  On the chip a solve of a
+ * million cells or more has every CU to itself for up to 4096 CG passes at a
+ * time (35 ms at 2048^2), which kernels of other streams wait for; ask for a
+ * tile where they must not.
  * Rebuilds the plan's block table (synchronous): PI_ERR_OOM if that fails,
  * and then pi_solve, pi_source, pi_apply and pi_time_kernel on the plan
  * return PI_ERR_OOM until a later pi_set_tile succeeds.

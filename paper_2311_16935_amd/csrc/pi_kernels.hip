@@ -1090,8 +1090,9 @@ __global__ __launch_bounds__(kBlock) void k_cg_step(const BlockEnt *tab, const I
 // pass that stores q takes 32.)  p_{k-2} is what the buffer that takes p_k
 // still holds.  A p_{k-1} is formed with the operator and operand values
 // the previous pass used for q_{k-1}, in the same order, so r_k, p_k and the
-// sums are those of the stored-q pass bit for bit.  The first pass of an
-// outer step (k_cg_first) is unchanged.
+// sums are those of the stored-q pass bit for bit.  Pass 0 of an outer
+// step is k_cg_rq_first, which writes nothing; with the fixed point's operator, or
+// a single inner iteration, it is k_cg_first, as where q is stored.
 //
 // Work is split by where the counter codes are constant: the planes 3 ..
 // nm-4 of rows 3 .. ny-4 of every wave strip, where every code a pass looks

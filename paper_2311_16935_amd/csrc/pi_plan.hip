@@ -670,7 +670,7 @@ extern "C" pi_status pi_plan(int ndim, const int64_t dims[3], const double spaci
     return PI_ERR_DEVICE;
   }
   // solved on the chip where it fits.  FP64 solves of the paper's iteration
-  // stream on grids with missing data and in the cell-centred scheme:
+  // stream on grids planned with a mask and in the cell-centred scheme:
   // rounding grows along their trajectories (386 x 301, 5 % missing: sums in
   // another order, 1e-16 apart, move the 40th iterate by up to 2e-10 and the
   // 60th by 5e-6 of its norm; cell-centred 130 x 91: 6e-11 after 30; the

@@ -39,7 +39,11 @@
 // all take the same scalars and decisions and results do not depend on
 // scheduling.  Workgroups wait for each other: launches of more than one
 // workgroup per grid are cooperative (all resident at once), and a wait that
-// outlasts kPatience ends the solve with PI_ERR_DEVICE instead of spinning on.
+// outlasts kPatience ends the solve with PI_ERR_DEVICE instead of spinning on,
+// whichever workgroup waited (res_late).
+//
+// A published value with its tag in one word is how collective libraries send
+// short messages (their low-latency protocols).
 #include <hip/hip_runtime.h>
 
 #include <math.h>

@@ -114,8 +114,9 @@ hipError_t capture(const Launcher &L, hipStream_t cap, int inner, bool bicg, hip
 }
 
 // Synchronisations (2-10 us each) of one on-chip launch, so that other work
-// on the device gets its turn and, in a batch, waiting grids get the
-// workgroups of finished ones.
+// on the device gets its turn (work of another stream beside a 2048^2 solve: after
+// 34 ms; beside 101^2, which leaves CUs free, at once) and, in a batch, waiting
+// grids get the workgroups of finished ones.
 constexpr int kResSyncs = 4096;
 int64_t resident_chunk(int inner) { return std::max(1, kResSyncs / (inner + 1)); }
 
