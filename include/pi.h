@@ -327,8 +327,10 @@ pi_status pi_time_kernel(pi_plan_t plan, int kernel, int32_t reps, double *avg_m
  * pi_get_cg_recompute -- 1 if the plan's inner CG passes (after the first
  * of each outer step) evaluate q = M p_{k-1} again where they need it
  * instead of storing q and reading it back, else 0 (also for NULL).  The
- * iterates are the same bit for bit; a pass then moves 24 bytes per cell
- * (reads r, p and the correction, writes them) instead of 32.  Chosen for
+ * iterates are the same bit for bit; a pass then moves 16 and 28 bytes per cell
+ * in turn (r and p in and out; every second pass also adds two terms to the
+ * correction; with PI_FIXED_POINT_CG every pass adds one, 24 bytes) instead of
+ * 32.  Chosen for
  * 3-D FP32 CG plans without missing data at four cells per lane whose rows
  * fit one wave strip (nx <= 256) or split over as many overlapping wave
  * windows (owning 252 cells at the row ends, 248 between them) as 256-cell
