@@ -160,9 +160,10 @@ inline double batch_chip_us(const Inst &in, bool fp64) {
 }
 
 // Microseconds a grid adds to a streaming pass over many: per block, by cells
-// per lane, for segments of four planes.  Each pass takes kStreamUs besides for
-// every launch shape among the grids.
-constexpr double kStreamUs = 11.0;
+// per lane, for segments of four planes.  For every launch shape among the grids
+// each pass takes kStreamUs besides, and the call kStreamStartUs to capture its
+// graph.
+constexpr double kStreamUs = 11.0, kStreamStartUs = 450.0;
 inline double batch_stream_us(const Inst &in, bool fp64) {
   const int v = in.vw == 4 ? 2 : in.vw == 2 ? 1 : 0;
   constexpr double face[3] = {0.0065, 0.010, 0.020}, face64[3] = {0.009, 0.018, 0.045}, cell[3] = {0.0103, 0.018, 0.036};
@@ -195,7 +196,7 @@ inline void batch_routes(std::vector<Inst> &insts, bool fp64, int max_wg, int sy
     longest = std::max(longest, left[i]);
     stream += left[i] * batch_stream_us(in, fp64);
   }
-  stream += kStreamUs * longest * (double)std::count(shape, shape + kShapes, true);
+  stream += (kStreamUs * longest + kStreamStartUs) * (double)std::count(shape, shape + kShapes, true);
   while (!todo.empty() || !on.empty()) {
     if (!res_admit(todo, on, max_wg, [&](int64_t i) { return insts[i].res_nwg; })) return;
     double us = 0.0;

@@ -114,7 +114,7 @@ CASES = [
 ]
 
 
-def routes(tmp_path, cases):
+def routes(tmp_path, cases, steps=24):
     hipcc = shutil.which("hipcc") or "/opt/rocm/bin/hipcc"
     if not os.path.exists(hipcc):
         pytest.skip("hipcc not available")
@@ -127,7 +127,7 @@ def routes(tmp_path, cases):
     lines = []
     for (nx, ny, nz), n, fp64, cc, opl, extra, cus in cases:
         e = extra or (0, 0, 0)
-        lines.append(f"{nx} {ny} {nz} {n} {fp64} {cc} {opl} {cus} {1 if opl else 24} {e[0]} {e[1]} {e[2]}")
+        lines.append(f"{nx} {ny} {nz} {n} {fp64} {cc} {opl} {cus} {1 if opl else steps} {e[0]} {e[1]} {e[2]}")
     out = subprocess.run([str(exe)], input="\n".join(lines), capture_output=True, text=True, timeout=120, check=True)
     return [tuple(int(v) for v in ln.split()) for ln in out.stdout.splitlines()]
 
@@ -140,6 +140,15 @@ def test_batches_go_where_they_are_faster(tmp_path):
         case = (dims, n, fp64, cc, opl, extra)
         assert fits == 1, case
         assert on_chip == (n + extra_fits if chip else 0), case
+
+
+def test_short_calls_do_not_pay_for_a_graph(tmp_path):
+    """Few outer steps: the capture of the streaming graph costs more than the rounds on the chip."""
+    cases = [((101, 101, 1), 24), ((300, 200, 1), 8), ((64, 64, 1), 1), ((64, 64, 1), 200), ((200, 199, 1), 30),
+             ((1000, 1000, 1), 4), ((101, 101, 1), 100)]  # at 0 steps 0.3 and 0.7, 0.3 and 0.9, 0.2 and 0.6 ms, ...
+    for steps in (0, 1, 2, 5):
+        got = routes(tmp_path, [c + (0, 0, 0, None, 256) for c in cases], steps)[3:]
+        assert [g[2] for g in got] == [c[1] for c in cases], steps
 
 
 def test_a_grid_that_fits_no_device_is_left_for_the_rounds_to_report(tmp_path):
